@@ -193,4 +193,42 @@ struct Tab {
 template <int D, int P>
 inline constexpr Tab<D, P> kTab{};
 
+// One-dimensional factors of the basis at the P+1 Gauss points: P_n, P_n'
+// and the weights.  Every table above is a product of these, so the stage
+// kernels contract one axis at a time (sum factorisation).
+template <int P>
+struct Rule1 {
+    double val[P + 1][P + 1] = {}, der[P + 1][P + 1] = {}, w[P + 1] = {};
+    constexpr Rule1()
+    {
+        for (int q = 0; q <= P; ++q) {
+            w[q] = gl_w(P + 1, q);
+            for (int n = 0; n <= P; ++n) {
+                val[q][n] = leg(n, gl_x(P + 1, q));
+                der[q][n] = dleg(n, gl_x(P + 1, q));
+            }
+        }
+    }
+};
+template <int P>
+inline constexpr Rule1<P> kRule{};
+
+// Position of P_i P_j in the graded two-axis basis (i on the first axis)
+constexpr int mode2(int i, int j) { return (i + j) * (i + j + 1) / 2 + j; }
+
+// Modes of a face of a d-dimensional cell: the total-degree products in the
+// remaining axes (lower first)
+template <int D, int P>
+constexpr int face_modes() { return D == 2 ? P + 1 : (P + 1) * (P + 2) / 2; }
+
+// Face mode of cell mode m on the faces normal to axis a
+template <int D, int P>
+constexpr int face_mode(int m, int a)
+{
+    if (D == 2) return kTab<D, P>.e[m][1 - a];
+    return a == 0 ? mode2(kTab<D, P>.e[m][1], kTab<D, P>.e[m][2])
+                  : (a == 1 ? mode2(kTab<D, P>.e[m][0], kTab<D, P>.e[m][2])
+                            : mode2(kTab<D, P>.e[m][0], kTab<D, P>.e[m][1]));
+}
+
 } // namespace dgk

@@ -16,6 +16,7 @@
 #include "kernels_ipdg.hpp"
 #include "kernels_mapped.hpp"
 #include "kernels_mfma.hpp"
+#include "kernels_points.hpp"
 #include "launch.hpp"
 
 #ifndef DG_D
@@ -98,8 +99,10 @@ int stage_rows_options(int N, int *rows, int max_options, bool fp32)
 }
 
 template <int D, int P, typename T, int EQ = EQ_EULER, bool MF = false>
-hipError_t launch_stage_cell(const StageArgs &a, int gm, int om, bool lim, const StageShape &sh, hipStream_t s)
+hipError_t launch_stage_cell(const StageArgs &args, int gm, int om, bool lim, const StageShape &sh, hipStream_t s)
 {
+    StageArgs a = args;
+    a.inv_n = unsigned((65536 + a.N - 1) / a.N);
     // slab of `rows` layers along the last axis within the thread budget
     const int layer = D == 2 ? a.N : a.N * a.N;
     int rows = sh.rows;
@@ -110,7 +113,14 @@ hipError_t launch_stage_cell(const StageArgs &a, int gm, int om, bool lim, const
     if (!rows_ok<D, P, T>(a.N, rows)) return hipErrorInvalidValue;
     const int nslab = rows * layer;
     const long items = long(a.nleaves) * (a.N / rows);
+    // the face exchange (point by point: face points in chunks; axis by axis:
+    // the face modes of every slab cell and of the cells outside), and the
+    // workgroup maximum of the CFL rate
     size_t lds = sizeof(double) * (D + 2) * face_chunk<D, P>() * nslab;
+    if constexpr (by_axis<D, P, T>()) {
+        lds = sizeof(double) * stage_lds_values<D, P, nvar<D, EQ>()>(a.N, rows);
+        if (lds < sizeof(double) * size_t(nslab)) lds = sizeof(double) * size_t(nslab);
+    }
     if constexpr (MF) {
         // whole waves only; the volume phase's per-wave LDS regions alias the
         // face exchange's buffer

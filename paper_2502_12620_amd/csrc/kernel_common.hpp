@@ -303,6 +303,7 @@ struct StageArgs {
     const int *work;      // leaf indices to process (null: 0 .. nleaves-1)
     const int *leaf_member; // member forest of each leaf (indexes dt), or null
     int conservative;     // mortar on hanging coarse faces
+    unsigned inv_n;       // ceil(2^16 / N), set by the launcher (div_n)
     // CFL time step fused into the stages (OUT_RK only): when rate_in is
     // set, dt = cfl / max rate read from *rate_in (written by the previous
     // step's last stage) and workgroup 0 stores it to dt_out; otherwise dt

@@ -2,13 +2,12 @@
 // Eq. 15-17) and the residual of the Galerkin weak form (Sec. 2, Eq. 3-5),
 // optionally fused with the SSP-RK3 stage update.
 //
-// One workgroup per leaf, one thread per cell.  The thread keeps its cell's
-// coefficients K[var][mode] and residual R[var][mode] in registers; the
-// basis tables are compile-time constants, so after full unrolling every
-// table entry is an immediate and structural zeros disappear.  The flux of
-// each face inside the block is computed once: the + trace of every cell
-// goes through LDS to its + neighbour, which computes the Rusanov flux and
-// sends it back through LDS.
+// One thread per cell.  The thread keeps its cell's coefficients K[var][mode]
+// and residual R[var][mode] in registers; the basis tables are compile-time
+// constants and every contraction goes one axis at a time.  The flux of each
+// face inside a workgroup's slab of cells is computed once: the + trace of
+// every cell goes through LDS to its + neighbour, which computes the Rusanov
+// flux and sends it back through LDS, both as the face's modes.
 #pragma once
 
 #include <type_traits>
@@ -20,12 +19,6 @@ namespace dgk {
 // one cell's coefficients (or residual) per variable and mode
 template <int D, int P>
 using CellCoef = double[D + 2][Tab<D, P>::NB];
-
-// Number of face points exchanged through LDS at once: all of them in 2-D,
-// one at a time in 3-D (keeps the register budget to one cell's state and
-// residual).
-template <int D, int P>
-constexpr int face_chunk() { return D == 2 ? (P == 3 ? 2 : Tab<D, P>::NF) : 1; }
 
 // Full unrolling over the quadrature points makes every table entry an
 // immediate.  In 3-D the unrolled code and its live ranges outgrow the
@@ -78,8 +71,9 @@ __device__ __forceinline__ void trace_eo_mem(const double *__restrict__ coef, lo
 // Conservative hanging-face flux: the coarse cell integrates the Rusanov
 // flux over the 2^(d-1) fine sub-faces at the fine Gauss points, with the
 // fine cells' own traces, and lifts it with its own basis evaluated at the
-// mapped points (tangential xi = (xi_fine + sigma)/2).
-template <int D, int P, int A, int EQ, typename T>
+// mapped points (tangential xi = (xi_fine + sigma)/2).  MASS: R is M^-1
+// times the weak form's right-hand side; otherwise that right-hand side.
+template <int D, int P, int A, int EQ, typename T, bool MASS>
 __device__ __forceinline__ void mortar_lift(const StageArgs &g, const T (&K)[nvar<D, EQ>()][Tab<D, P>::NB],
                                             T (&R)[nvar<D, EQ>()][Tab<D, P>::NB], int side, const FaceLink L, int t,
                                             T scale)
@@ -132,7 +126,7 @@ __device__ __forceinline__ void mortar_lift(const StageArgs &g, const T (&K)[nva
 #pragma unroll
                 for (int m = 0; m < NB; ++m) {
                     const double c = leg(kTab<D, P>.e[m][TA], x0) * (D == 3 ? leg(kTab<D, P>.e[m][TBX], x1) : 1.0) *
-                                     kTab<D, P>.inv_mass[m];
+                                     (MASS ? kTab<D, P>.inv_mass[m] : 1.0);
                     if (c != 0.0) {
                         const double sg = side > 0 ? -1.0 : ((kTab<D, P>.e[m][A] % 2) ? -1.0 : 1.0);
                         R[v][m] = fma(T(sg * c), f, R[v][m]);
@@ -205,101 +199,6 @@ __device__ __forceinline__ void comb_any(int child, const double *k, double *gk)
     }
 }
 
-// Far-side traces of block face (A, side) at the FCH face points starting
-// at f0, for the cell with tangential index t (the far polynomial touches
-// the face with its -side side):
-//  - guard-buffer mode: the stored guard cell;
-//  - inline mode: the same-level neighbour cell (Eq. 15), the split of the
-//    coarser neighbour cell (Eq. 16), the combine of the 2^d finer cells
-//    (Eq. 17), or at an outflow boundary the mirror image, whose trace is
-//    the own trace.
-template <int D, int P, int A, int GM, int FCH, int NV, typename T>
-__device__ __forceinline__ void far_traces(const StageArgs &g, const T (&K)[NV][Tab<D, P>::NB], int leaf, int side,
-                                           int t, const FaceLink &L, int f0, T (&Tr)[FCH][NV])
-{
-    constexpr int NB = Tab<D, P>::NB;
-    const int N = g.N, ncell = D == 2 ? N * N : N * N * N, nfc = D == 2 ? N : N * N;
-    const long sv = long(NB) * ncell;
-    const int face = 2 * A + (side > 0);
-    auto traces_of = [&](const T *kv, int v, int poly_side) {
-#pragma unroll
-        for (int fi = 0; fi < FCH; ++fi) {
-            T e, o;
-            trace_eo<D, P, T>(kv, A, f0 + fi, e, o);
-            Tr[fi][v] = poly_side > 0 ? e + o : e - o;
-        }
-    };
-    if (GM == GUARD_TRACE) {
-        constexpr int NF = Tab<D, P>::NF;
-        const double *gt = g.guard + ((long(leaf) * 2 * D + face) * NV * NF) * nfc + t;
-#pragma unroll
-        for (int fi = 0; fi < FCH; ++fi)
-#pragma unroll
-            for (int v = 0; v < NV; ++v) Tr[fi][v] = T(gt[(long(v) * NF + f0 + fi) * nfc]);
-        return;
-    }
-    if (GM == GUARD_BUFFER) {
-        const double *gk = g.guard + ((long(leaf) * 2 * D + face) * NV * NB) * nfc + t;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            T kv[NB];
-#pragma unroll
-            for (int m = 0; m < NB; ++m) kv[m] = T(gk[(long(v) * NB + m) * nfc]);
-            traces_of(kv, v, -side);
-        }
-        return;
-    }
-    if (L.type == dgamr::LINK_BOUNDARY) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) traces_of(K[v], v, side);
-    } else if (L.type == dgamr::LINK_SAME) {
-        const int c = same_cell(A, side, t, N, D);
-        const double *nk = g.us + long(L.nbr[0]) * NV * sv + c;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            T kv[NB];
-#pragma unroll
-            for (int m = 0; m < NB; ++m) kv[m] = T(nk[v * sv + m * ncell]);
-            traces_of(kv, v, -side);
-        }
-    } else if (L.type == dgamr::LINK_COARSE) {
-        const int c = coarse_cell(A, side, t, L.off, N, D);
-        const int child = coarse_child(A, side, t, N, D);
-        const double *ck = g.us + long(L.nbr[0]) * NV * sv + c;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            T kv[NB], gv[NB];
-#pragma unroll
-            for (int m = 0; m < NB; ++m) kv[m] = T(ck[v * sv + m * ncell]);
-            split_any<D, P, T>(child, kv, gv);
-            traces_of(gv, v, -side);
-        }
-    } else { // LINK_FINE
-        const double *fk = g.us + long(link_nbr(L, fine_block(t, N, D))) * NV * sv;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            T gv[NB];
-#pragma unroll
-            for (int m = 0; m < NB; ++m) gv[m] = T(0);
-#pragma unroll
-            for (int ch = 0; ch < (1 << D); ++ch) {
-                const int fc = fine_cell(A, side, t, ch, N, D);
-                T kv[NB];
-#pragma unroll
-                for (int n = 0; n < NB; ++n) kv[n] = T(fk[v * sv + n * ncell + fc]);
-#pragma unroll
-                for (int m = 0; m < NB; ++m)
-#pragma unroll
-                    for (int n = 0; n < NB; ++n) {
-                        const double cc = kTab<D, P>.comb[ch][m][n];
-                        if (cc != 0.0) gv[m] = fma(T(cc), kv[n], gv[m]);
-                    }
-            }
-            traces_of(gv, v, -side);
-        }
-    }
-}
-
 // Far-side polynomial of block face (A, side) for the cell with tangential
 // index t, per variable (its traces at the face are taken at -side):
 //  - guard-buffer mode: the stored guard cell;
@@ -365,6 +264,38 @@ __host__ __device__ __forceinline__ void far_poly(const StageArgs &g, const T (&
                         if (cc != 0.0) Kf[v][m] = fma(T(cc), kv[n], Kf[v][m]);
                     }
             }
+        }
+    }
+}
+
+// Variable v of the far-side polynomial of a hanging block face (a, side) for
+// the cell with tangential index t: the split of the coarser neighbour cell
+// (Eq. 16) or the combine of the 2^d finer cells (Eq. 17).
+template <int D, int P, int NV>
+__device__ __forceinline__ void hanging_var(const StageArgs &g, int v, int a, int side, int t, const FaceLink &L,
+                                            double *kf)
+{
+    constexpr int NB = Tab<D, P>::NB;
+    const int N = g.N, ncell = D == 2 ? N * N : N * N * N;
+    const long sv = long(NB) * ncell;
+    if (L.type == dgamr::LINK_COARSE) {
+        const int c = coarse_cell(a, side, t, L.off, N, D);
+        const double *ck = g.us + long(L.nbr[0]) * NV * sv + v * sv + c;
+        double kv[NB];
+#pragma unroll
+        for (int m = 0; m < NB; ++m) kv[m] = ck[m * ncell];
+        split_any<D, P, double>(coarse_child(a, side, t, N, D), kv, kf);
+    } else { // LINK_FINE
+        const double *fk = g.us + long(link_nbr(L, fine_block(t, N, D))) * NV * sv + v * sv;
+#pragma unroll
+        for (int m = 0; m < NB; ++m) kf[m] = 0.0;
+#pragma unroll
+        for (int ch = 0; ch < (1 << D); ++ch) {
+            const int fc = fine_cell(a, side, t, ch, N, D);
+            double kv[NB];
+#pragma unroll
+            for (int n = 0; n < NB; ++n) kv[n] = fk[n * ncell + fc];
+            comb_any<D, P>(ch, kv, kf);
         }
     }
 }
@@ -480,12 +411,339 @@ __device__ __forceinline__ void limit_cell(CellCoef<D, P> &K, double gamma, cons
         }
 }
 
+// ------------------------------------------------------------------ sum-factorised contractions
+// What bounds the stage: memory latency and the instructions of one wave's
+// chain, with two or three waves per SIMD.  Contracting one axis at a time
+// takes 9 points x 6 modes at 2-D degree 2 from 54 multiply-adds per variable
+// to 27, and the faces exchange their modes with two barriers per axis
+// instead of four per chunk of face points; the traces from outside the slab
+// are gathered densely, one exposed memory latency for all axes.  Measured
+// against the contraction point by point (uniform vortex forests, two steps):
+// 2-D, degree 1, 128^2 roots of 16^2 cells 1.71 -> 1.49 ms; degree 2, 64^2
+// roots 0.98 -> 0.79 ms; 3-D degree 1, 16^3 roots of 8^3 cells 2.75 -> 2.07 ms.
+
+// Coefficients of the trace of one variable's polynomial on the face of
+// axis A at xi_A = s (s = +1 or -1) in the face modes: sum_i s^i K_(i, f).
+template <int D, int P, int A>
+__device__ __forceinline__ void face_trace(const double *K, double s, double *tr)
+{
+    constexpr int NB = Tab<D, P>::NB, NBF = face_modes<D, P>();
+    double odd[NBF];
+    // modes come in ascending degree, so the first of a face mode has i = 0
+#pragma unroll
+    for (int m = 0; m < NB; ++m) {
+        const int f = face_mode<D, P>(m, A), i = kTab<D, P>.e[m][A];
+        if (i == 0) tr[f] = K[m];
+        else if (i == 1) odd[f] = K[m];
+        else if (i % 2 == 0) tr[f] += K[m];
+        else odd[f] += K[m];
+    }
+#pragma unroll
+    for (int m = 0; m < NB; ++m) // the face modes that have odd terms
+        if (kTab<D, P>.e[m][A] == 1) tr[face_mode<D, P>(m, A)] = fma(s, odd[face_mode<D, P>(m, A)], tr[face_mode<D, P>(m, A)]);
+}
+
+// Numerical flux in the +e_A direction between the own state Uo and the
+// neighbour's Un across the face on the `side` (+1 / -1) of axis A, the
+// same value to the last bit from both sides: Rusanov (Eq. 5), or upwind
+// for scalar convection (num_flux with left and right ordered by the side).
+template <int D, int A, int EQ, class Args>
+__device__ __forceinline__ void side_flux(const Args &g, const double *Uo, const double *Un, double side, double gamma, double *Phi)
+{
+    if constexpr (EQ == EQ_ADVECTION) {
+        const double a = g.vel[A];
+        Phi[0] = 0.5 * (a * (Uo[0] + Un[0]) - side * (fabs(a) * (Un[0] - Uo[0])));
+    } else {
+        constexpr int NV = D + 2;
+        const double gm1 = gamma - 1.0;
+        const double ro = recip(Uo[0]), rn = recip(Un[0]);
+        const double po = pressure_r<D>(Uo, gm1, ro), pn = pressure_r<D>(Un, gm1, rn);
+        const double uo = Uo[1 + A] * ro, un = Un[1 + A] * rn;
+        const double ao = fabs(uo) + sqrt_nn(gamma * po * ro), an = fabs(un) + sqrt_nn(gamma * pn * rn);
+        const double alpha = side * (ao > an ? ao : an);
+        double Fo[NV], Fn[NV];
+        euler_flux<D, A>(Uo, uo, po, Fo);
+        euler_flux<D, A>(Un, un, pn, Fn);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Phi[v] = 0.5 * ((Fo[v] + Fn[v]) - alpha * (Un[v] - Uo[v]));
+    }
+}
+
+// Flux of one face in its face modes: both traces evaluated at the face
+// points row by row, the numerical flux there, and its projection int Phi
+// phi_f.  own(v, tr) gives the own trace's modes of variable v, nbr(v, f) the
+// neighbour's mode f.
+template <int D, int P, int A, int EQ, class Args, class Own, class Nbr>
+__device__ __forceinline__ void face_flux(double side, double gamma, const Args &gv, Own &&own, Nbr &&nbr,
+                                          double (&Phi)[nvar<D, EQ>()][face_modes<D, P>()])
+{
+    constexpr int NV = nvar<D, EQ>(), NBF = face_modes<D, P>(), Q = P + 1;
+    // one row of points along the lower tangential axis: ro, rn its
+    // coefficients, acc the projection of the flux along the row
+    auto row = [&](const double (&ro)[NV][Q], const double (&rn)[NV][Q], double (&acc)[NV][Q]) __attribute__((always_inline)) {
+        static_for<0, Q>([&](auto qv) __attribute__((always_inline)) {
+            constexpr int q = qv;
+            double Uo[NV], Un[NV], F[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                Uo[v] = ro[v][0];
+                Un[v] = rn[v][0];
+#pragma unroll
+                for (int j = 1; j < Q; ++j) {
+                    const double c = kRule<P>.val[q][j];
+                    if (c != 0.0) {
+                        Uo[v] = fma(c, ro[v][j], Uo[v]);
+                        Un[v] = fma(c, rn[v][j], Un[v]);
+                    }
+                }
+            }
+            side_flux<D, A, EQ>(gv, Uo, Un, side, gamma, F);
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    const double c = kRule<P>.w[q] * kRule<P>.val[q][j];
+                    if (c != 0.0) acc[v][j] = q == 0 ? c * F[v] : fma(c, F[v], acc[v][j]);
+                    else if (q == 0) acc[v][j] = 0.0;
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    double tr[NV][NBF];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) own(v, tr[v]);
+    if constexpr (D == 2) {
+        double rn[NV][Q];
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int f = 0; f < NBF; ++f) rn[v][f] = nbr(v, f);
+        row(tr, rn, Phi);
+    } else {
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int f = 0; f < NBF; ++f) Phi[v][f] = 0.0;
+        static_for<0, Q>([&](auto rv) __attribute__((always_inline)) {
+            constexpr int r = decltype(rv)::value;
+            double ro[NV][Q], rn[NV][Q], acc[NV][Q];
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    ro[v][j] = tr[v][mode2(j, 0)];
+                    rn[v][j] = nbr(v, mode2(j, 0));
+#pragma unroll
+                    for (int k = 1; j + k < Q; ++k) {
+                        const double c = kRule<P>.val[r][k];
+                        if (c != 0.0) {
+                            ro[v][j] = fma(c, tr[v][mode2(j, k)], ro[v][j]);
+                            rn[v][j] = fma(c, nbr(v, mode2(j, k)), rn[v][j]);
+                        }
+                    }
+                }
+            row(ro, rn, acc);
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int j = 0; j < Q; ++j)
+#pragma unroll
+                    for (int k = 0; j + k < Q; ++k) {
+                        const double c = kRule<P>.w[r] * kRule<P>.val[r][k];
+                        if (c != 0.0) Phi[v][mode2(j, k)] = fma(c, acc[v][j], Phi[v][mode2(j, k)]);
+                    }
+        });
+    }
+}
+
+// R_m -= side^(m_A + 1) (2/h_A) Phi_f(m): the face's flux modes lifted onto
+// the cell's modes (before M^-1)
+template <int D, int P, int A, int EQ>
+__device__ __forceinline__ void lift(const double (&Phi)[nvar<D, EQ>()][face_modes<D, P>()], int side, double sc,
+                                     double (&R)[nvar<D, EQ>()][Tab<D, P>::NB])
+{
+    constexpr int NV = nvar<D, EQ>(), NB = Tab<D, P>::NB;
+    const double even = side < 0 ? sc : -sc;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int m = 0; m < NB; ++m)
+            R[v][m] = fma(kTab<D, P>.e[m][A] % 2 == 0 ? even : -sc, Phi[v][face_mode<D, P>(m, A)], R[v][m]);
+}
+
+// x / N of a cell index x with g.inv_n = ceil(2^16 / N): exact for x < 4096
+// and N <= 16
+__device__ __forceinline__ int div_n(int x, unsigned inv_n) { return int((unsigned(x) * inv_n) >> 16); }
+
+// Faces normal to axis a between a slab's cells and the cells outside it:
+// count(a) on either side, numbered over the slab's other axes; all sides of
+// all axes in sequence (the extra LDS slots): first(a) of the lower axes.
+template <int D>
+struct SlabFaces {
+    int N, rows, layer;
+    unsigned inv_n;
+    __device__ __forceinline__ int side_faces() const { return D == 2 ? rows : rows * N; }
+    __device__ __forceinline__ int count(int a) const { return a == D - 1 ? layer : side_faces(); }
+    __device__ __forceinline__ int first(int a) const
+    {
+        return a < D ? a * 2 * side_faces() : 2 * ((D - 1) * side_faces() + layer);
+    }
+    // slab cell at face b on the given side
+    __device__ __forceinline__ int cell(int a, int side, int b) const
+    {
+        if (a == D - 1) return b + (side < 0 ? 0 : (rows - 1) * layer);
+        const int n = side < 0 ? 0 : N - 1;
+        if (a == 0) return n + N * b;
+        const int k = div_n(b, inv_n);
+        return b - N * k + N * n + layer * k;
+    }
+    // face number of a cell next to either side
+    __device__ __forceinline__ int slot(int a, int lc) const
+    {
+        const int j = div_n(lc, inv_n);
+        if (a == 0) return j;
+        const int k = D == 3 ? div_n(j, inv_n) : 0;
+        return a == D - 1 ? lc - (D == 3 ? k * layer : j * N) : lc - j * N + N * k;
+    }
+    __device__ __forceinline__ void ijk(int cell, int *x) const
+    {
+        const int j = div_n(cell, inv_n), k = D == 3 ? div_n(j, inv_n) : 0;
+        x[0] = cell - j * N;
+        x[1] = D == 3 ? j - k * N : j;
+        x[2] = k;
+    }
+};
+
+// doubles in the dynamic LDS of a slab of `rows` layers
+template <int D, int P, int NV>
+constexpr size_t stage_lds_values(int N, int rows)
+{
+    const size_t layer = D == 2 ? N : size_t(N) * N, side = size_t(rows) * (D == 2 ? 1 : N);
+    return size_t((NV * face_modes<D, P>()) | 1) * (rows * layer + 2 * ((D - 1) * side + layer));
+}
+
+// Volume integral of one cell by sum factorisation: R_m += sum_q w_q
+// F_a(U_q) (2/h_a) dphi_m/dxi_a.  The state along a row of points (x) comes
+// from the row's coefficients; the row's fluxes are contracted along x
+// before they reach the modes.
+template <int D, int P, int EQ, class Args>
+__device__ __forceinline__ void volume_rows(const double (&K)[nvar<D, EQ>()][Tab<D, P>::NB],
+                                            double (&R)[nvar<D, EQ>()][Tab<D, P>::NB], const double *scale, double gm1,
+                                            const Args &gv)
+{
+    constexpr int NV = nvar<D, EQ>(), NB = Tab<D, P>::NB, Q = P + 1, NB2 = Q * (Q + 1) / 2;
+    // C: the polynomial in (x, y) on the plane qz; qz = 0 and unit weight in 2-D
+    auto plane = [&](const double (&C)[NV][NB2], auto qzv) __attribute__((always_inline)) {
+        constexpr int qz = decltype(qzv)::value;
+        static_for<0, Q>([&](auto qyv) __attribute__((always_inline)) {
+            constexpr int qy = qyv;
+            double row[NV][Q], rx[NV][P], ry[NV][P], rz[NV][P];
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    row[v][i] = C[v][mode2(i, 0)];
+#pragma unroll
+                    for (int j = 1; i + j < Q; ++j) {
+                        const double c = kRule<P>.val[qy][j];
+                        if (c != 0.0) row[v][i] = fma(c, C[v][mode2(i, j)], row[v][i]);
+                    }
+                }
+            static_for<0, Q>([&](auto qxv) __attribute__((always_inline)) {
+                constexpr int qx = qxv;
+                double U[NV];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    U[v] = row[v][0];
+#pragma unroll
+                    for (int i = 1; i < Q; ++i) {
+                        const double c = kRule<P>.val[qx][i];
+                        if (c != 0.0) U[v] = fma(c, row[v][i], U[v]);
+                    }
+                }
+                double rinv = 0.0, p = 0.0;
+                if constexpr (EQ == EQ_EULER) {
+                    rinv = recip(U[0]);
+                    p = pressure_r<D>(U, gm1, rinv);
+                }
+                static_for<0, D>([&](auto Ai) __attribute__((always_inline)) {
+                    constexpr int A = Ai;
+                    double F[NV];
+                    if constexpr (EQ == EQ_ADVECTION) {
+                        F[0] = (gv.vel[A] * scale[A]) * U[0];
+                    } else { // the flux along A times 2/h_A
+                        const double us = U[1 + A] * (rinv * scale[A]), ps = p * scale[A];
+                        F[0] = U[0] * us;
+#pragma unroll
+                        for (int b = 0; b < D; ++b) F[1 + b] = U[1 + b] * us;
+                        F[1 + A] += ps;
+                        F[D + 1] = fma(U[D + 1], us, ps * (U[1 + A] * rinv));
+                    }
+#pragma unroll
+                    for (int i = 0; i < P; ++i) {
+                        // x: modes i + 1 through their derivative; y, z: modes
+                        // i < P (the other factor has degree >= 1)
+                        const double c = kRule<P>.w[qx] * (A == 0 ? kRule<P>.der[qx][i + 1] : kRule<P>.val[qx][i]);
+                        double(&r)[NV][P] = A == 0 ? rx : (A == 1 ? ry : rz);
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) {
+                            if (c != 0.0) r[v][i] = qx == 0 ? c * F[v] : fma(c, F[v], r[v][i]);
+                            else if (qx == 0) r[v][i] = 0.0;
+                        }
+                    }
+                });
+            });
+#pragma unroll
+            for (int m = 0; m < NB; ++m) {
+                const int i = kTab<D, P>.e[m][0], j = kTab<D, P>.e[m][1], k = kTab<D, P>.e[m][2];
+                const double wz = D == 3 ? kRule<P>.w[qz] : 1.0, vz = wz * (D == 3 ? kRule<P>.val[qz][k] : 1.0);
+                const double vy = kRule<P>.w[qy] * kRule<P>.val[qy][j], dy = kRule<P>.w[qy] * kRule<P>.der[qy][j];
+                if (i > 0 && vy != 0.0 && vz != 0.0) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) R[v][m] = fma(vy * vz, rx[v][i - 1], R[v][m]);
+                }
+                if (j > 0 && dy != 0.0 && vz != 0.0) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) R[v][m] = fma(dy * vz, ry[v][i], R[v][m]);
+                }
+                if (D == 3 && k > 0) {
+                    const double dz = wz * kRule<P>.der[qz][k];
+                    if (vy != 0.0 && dz != 0.0) {
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) R[v][m] = fma(vy * dz, rz[v][i], R[v][m]);
+                    }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    if constexpr (D == 2) {
+        plane(K, std::integral_constant<int, 0>{});
+    } else {
+        static_for<0, Q>([&](auto qzv) __attribute__((always_inline)) {
+            constexpr int qz = decltype(qzv)::value;
+            double C[NV][NB2];
+#pragma unroll
+            for (int m = 0; m < NB; ++m) {
+                const int f = mode2(kTab<D, P>.e[m][0], kTab<D, P>.e[m][1]), k = kTab<D, P>.e[m][2];
+                const double c = kRule<P>.val[qz][k];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    if (k == 0) C[v][f] = K[v][m];
+                    else if (c != 0.0) C[v][f] = fma(c, K[v][m], C[v][f]);
+                }
+            }
+            plane(C, qzv);
+        });
+    }
+}
+
 // ------------------------------------------------------------------ stage kernel
 // One thread per cell.  A workgroup covers a slab of `rows` layers of the
-// leaf along its last axis (the whole leaf in 2-D; in 3-D slabs of at most
-// 256 cells, so a thread may keep its cell's state and residual in up to
-// 512 registers); faces on a slab edge inside the leaf read the adjacent
-// layer straight from the stage input.
+// leaf along its last axis (in 3-D slabs of at most 256 cells from degree 2,
+// so a thread may keep its cell's state and residual in up to 512
+// registers); faces on a slab edge inside the leaf read the adjacent layer
+// straight from the stage input.
 // threads per workgroup: 3-D degree <= 1 keeps whole 512-cell leaves (the
 // state fits 256 registers); every other case uses slabs of <= 256 cells
 // (3-D degree 2 in FP32 at 512 threads spills ~600 bytes per lane)
@@ -529,26 +787,14 @@ constexpr int stage_min_waves()
     return P == 3 && sizeof(T) == 4 ? 2 : 1;
 }
 
-// T is the arithmetic type of the residual: double, or float for the FP32
-// path (state read as FP64 and rounded; the stage update, limiter and CFL
-// rate stay FP64).
 // One work item: slab `item` of the leaf list (all leaves, or the listed
 // ones), for the thread's cell.
-template <int D, int P>
-__device__ __forceinline__ void volume_mfma(const float (&K)[D + 2][Tab<D, P>::NB], float (&R)[D + 2][Tab<D, P>::NB],
-                                            float *lds, const float *scale, float gm1);
-template <int D, int P>
-constexpr int mfma_lds_floats();
-
-// MF: the volume integral on the matrix cores (FP32 Euler, whole waves of
-// cells; kernels_mfma.hpp)
-template <int D, int P, int GM, int OM, bool LIM, typename T, int EQ, bool MF = false>
+template <int D, int P, int GM, int OM, bool LIM, int EQ>
 __device__ __forceinline__ void stage_item(const StageArgs &g, int rows, int item, int total)
 {
-    constexpr int NV = nvar<D, EQ>(), NB = Tab<D, P>::NB, NQ = Tab<D, P>::NQ, NF = Tab<D, P>::NF;
-    constexpr int FCH = face_chunk<D, P>();
-    extern __shared__ double lds_d[];
-    T *lds = reinterpret_cast<T *>(lds_d);
+    constexpr int NV = nvar<D, EQ>(), NB = Tab<D, P>::NB, NBF = face_modes<D, P>();
+    constexpr int PITCH = (NV * NBF) | 1; // values per LDS slot: odd, so that the lanes spread over the banks
+    extern __shared__ double lds[];
 
     const int N = g.N, ncell = D == 2 ? N * N : N * N * N;
     const int layer = D == 2 ? N : N * N; // cells per layer of the last axis
@@ -559,8 +805,8 @@ __device__ __forceinline__ void stage_item(const StageArgs &g, int rows, int ite
     const int lc = threadIdx.x, nslab = rows * layer;
     const int cell = lc + k0 * layer;
     int ijk[3];
-    cell_ijk(cell, N, D, ijk);
-    const T scale[3] = {T(g.geo[leaf].scale[0]), T(g.geo[leaf].scale[1]), T(g.geo[leaf].scale[2])};
+    SlabFaces<D>{N, rows, layer, g.inv_n}.ijk(cell, ijk);
+    const double scale[3] = {g.geo[leaf].scale[0], g.geo[leaf].scale[1], g.geo[leaf].scale[2]};
     const long sv = long(NB) * ncell;
     const long base = long(leaf) * NV * sv + cell;
     // (v, m) plane of this leaf in array X: a workgroup-uniform address, so
@@ -569,18 +815,20 @@ __device__ __forceinline__ void stage_item(const StageArgs &g, int rows, int ite
     const unsigned uc = unsigned(cell);
     auto plane = [&](auto *X, int v, int m) __attribute__((always_inline)) { return X + (lbase + v * sv + long(m) * ncell); };
 
-    T K[NV][NB], R[NV][NB];
+    double K[NV][NB], R[NV][NB];
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
         for (int m = 0; m < NB; ++m) {
-            K[v][m] = T(plane(g.us, v, m)[uc]);
-            R[v][m] = T(0);
+            K[v][m] = plane(g.us, v, m)[uc];
+            R[v][m] = 0.0;
         }
 
-    // ---- volume integral: sum_q w_q F_a(U_q) (2/h_a) dphi_m/dxi_a / M_m
-    const T gamma = T(g.gamma), gm1 = T(g.gamma - 1.0);
-    // scalar convection: the velocity along the leaf's local axes, Q^T vel
+    // ---- volume integral: sum_q w_q F_a(U_q) (2/h_a) dphi_m/dxi_a, one axis
+    // contracted at a time: planes (3-D), rows along x, points.  R is the
+    // right-hand side of the weak form; M^-1 (diagonal) follows at the end.
+    const double gamma = g.gamma, gm1 = g.gamma - 1.0;
+    // scalar convection: the velocity along the leaf's local axes, Q^double vel
     // (Sec. 3.1 frames; the identity on aligned roots)
     struct {
         double vel[3];
@@ -596,228 +844,151 @@ __device__ __forceinline__ void stage_item(const StageArgs &g, int rows, int ite
     } else {
         gv.vel[0] = gv.vel[1] = gv.vel[2] = 0.0;
     }
-    auto vol_point = [&](auto qv) __attribute__((always_inline)) {
-        const int q = qv;
-        T U[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            T s = T(0);
-#pragma unroll
-            for (int m = 0; m < NB; ++m) {
-                const double c = kTab<D, P>.phi_v[q][m];
-                if (use_entry<D, P>(c)) s = fma(T(c), K[v][m], s);
-            }
-            U[v] = s;
-        }
-        T rinv = T(0), p = T(0);
-        if constexpr (EQ == EQ_EULER) {
-            rinv = recip(U[0]);
-            p = pressure_r<D, T>(U, gm1, rinv);
-        }
-        static_for<0, D>([&](auto Ai) __attribute__((always_inline)) {
-            constexpr int A = Ai;
-            T F[NV];
-            if constexpr (EQ == EQ_ADVECTION) F[0] = T(gv.vel[A]) * U[0];
-            else euler_flux<D, A, T>(U, U[1 + A] * rinv, p, F);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) F[v] *= scale[A];
-#pragma unroll
-            for (int m = 0; m < NB; ++m) {
-                const double c = kTab<D, P>.dproj[A][q][m];
-                // a mode of degree 0 along A has no derivative along A
-                if (kTab<D, P>.e[m][A] != 0 && use_entry<D, P>(c)) {
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) R[v][m] = fma(T(c), F[v], R[v][m]);
-                }
-            }
-        });
-    };
-    if constexpr (MF) {
-        static_assert(std::is_same<T, float>::value && EQ == EQ_EULER, "matrix-core volume: FP32 Euler");
-        float *wave_lds = reinterpret_cast<float *>(lds_d) + (threadIdx.x >> 6) * mfma_lds_floats<D, P>();
-        // the per-wave regions alias the face exchange and the CFL fold of
-        // the previous work item of a persistent workgroup: every wave
-        // leaves them before any wave writes here
-        __syncthreads();
-        volume_mfma<D, P>(K, R, wave_lds, scale, gm1);
-    } else if constexpr (unroll_points<D, P>()) {
-        static_for<0, NQ>(vol_point);
-    } else {
+    // ---- traces from outside the slab (block faces and slab edges) into their
+    // extra LDS slots, the faces of all axes dense over the threads and before
+    // the volume integral: one exposed memory latency
+    {
+        const SlabFaces<D> sf{N, rows, layer, g.inv_n};
+        const int total_faces = sf.first(D);
+        const int layer_faces = D == 2 ? N : N * N; // cells of a block face
 #pragma unroll 1
-        for (int q = 0; q < NQ; ++q) vol_point(q);
+        for (int e = lc; e < total_faces; e += nslab) {
+            // extra slot e: axis, side, face number
+            const int a = e < sf.first(1) ? 0 : (D == 2 || e < sf.first(2) ? 1 : 2), b = e - sf.first(a);
+            const int nE = sf.count(a), side = b < nE ? -1 : 1;
+            const int own = sf.cell(a, side, side < 0 ? b : b - nE), cell2 = own + k0 * layer;
+            int ijk2[3];
+            sf.ijk(cell2, ijk2);
+            const int ia2 = a == 0 ? ijk2[0] : (a == 1 ? ijk2[1] : ijk2[2]);
+            const bool at_face = ia2 == (side < 0 ? 0 : N - 1);
+            const FaceLink L = g.links[leaf * 2 * D + 2 * a + (side > 0)];
+            if (g.conservative && at_face && L.type == dgamr::LINK_FINE) continue; // mortar: its flux is not used
+            const int stride = a == 0 ? 1 : (a == 1 ? N : N * N);
+            const int t = face_t(ijk2, a, N, D);
+            double *const out = lds + PITCH * (nslab + e);
+            auto emit = [&](const double *kf, int v, double s) __attribute__((always_inline)) {
+                static_for<0, D>([&](auto Ai) __attribute__((always_inline)) {
+                    if (a == Ai) {
+                        double tr[NBF];
+                        face_trace<D, P, Ai>(kf, s, tr);
+#pragma unroll
+                        for (int f = 0; f < NBF; ++f) out[v * NBF + f] = tr[f];
+                    }
+                });
+            };
+            if (GM == GUARD_INLINE && at_face && (L.type == dgamr::LINK_COARSE || L.type == dgamr::LINK_FINE)) {
+                // hanging faces, one variable at a time
+#pragma unroll 1
+                for (int v = 0; v < NV; ++v) {
+                    double kf[NB];
+                    hanging_var<D, P, NV>(g, v, a, side, t, L, kf);
+                    emit(kf, v, double(-side));
+                }
+            } else {
+                // one source cell, every load issued before the first use: the
+                // neighbour cell at a slab edge or in the neighbour leaf, the
+                // guard cell, or (outflow) the own cell, whose trace is the
+                // mirror image's
+                const double *nk;
+                long step = ncell;
+                bool mirror = false;
+                if (!at_face) {
+                    nk = g.us + lbase + cell2 + side * stride;
+                } else if constexpr (GM == GUARD_BUFFER) {
+                    step = layer_faces;
+                    nk = g.guard + ((long(leaf) * 2 * D + 2 * a + (side > 0)) * NV * NB) * step + t;
+                } else {
+                    mirror = L.type == dgamr::LINK_BOUNDARY;
+                    nk = mirror ? g.us + lbase + cell2
+                                : g.us + long(L.nbr[0]) * NV * sv + same_cell(a, side, t, N, D);
+                }
+                double kf[NV][NB];
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+#pragma unroll
+                    for (int m = 0; m < NB; ++m) kf[v][m] = nk[(v * NB + m) * step];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) emit(kf[v], v, double(mirror ? side : -side));
+            }
+        }
+    }
+    if constexpr (P > 0) {
+        volume_rows<D, P, EQ>(K, R, scale, gm1, gv);
     }
 
-    // ---- surface integrals, one axis at a time
+    // ---- surface integrals, one axis at a time.  The trace of a cell on a
+    // face is a polynomial in the NBF face modes.  Its T+ goes into the
+    // cell's LDS slot, the traces from outside the slab into extra slots;
+    // the + neighbour (for the slab's last cells, one of the first nE
+    // threads) evaluates both traces at the face points, takes the flux,
+    // projects it onto the face modes and leaves those where it found T+, so
+    // an axis needs two barriers and every face of the slab is done once.
     static_for<0, D>([&](auto Ai) __attribute__((always_inline)) {
         constexpr int A = Ai;
         const int stride = A == 0 ? 1 : (A == 1 ? N : N * N);
         const int ia = ijk[A];
-        // neighbours reachable through LDS (inside this slab)
+        // neighbours inside this slab
         const bool in_m = A == D - 1 ? ia > k0 : ia > 0;
-        const bool in_p = A == D - 1 ? ia < k0 + rows - 1 : ia < N - 1;
-        const int t = face_t(ijk, A, N, D);
-        const T sc = scale[A];
-        const FaceLink Lm = g.links[leaf * 2 * D + 2 * A];
-        const FaceLink Lp = g.links[leaf * 2 * D + 2 * A + 1];
-        const bool mort_m = g.conservative && ia == 0 && Lm.type == dgamr::LINK_FINE;
-        const bool mort_p = g.conservative && ia == N - 1 && Lp.type == dgamr::LINK_FINE;
-        if (mort_m) mortar_lift<D, P, A, EQ, T>(g, K, R, -1, Lm, t, sc);
-        if (mort_p) mortar_lift<D, P, A, EQ, T>(g, K, R, +1, Lp, t, sc);
-        // In 3-D a cell has at most one side along A whose neighbour is not
-        // in the slab (slabs hold at least two layers or the whole leaf); the
-        // polynomial across it (the neighbour cell at a slab edge, or the
-        // far side of a block face: guard coefficients, or inline copy /
-        // split / combine / mirror) is built once here and its traces taken
-        // per face point.  Read per face point, the compiler hoists both
-        // sides' loads out of the point loop and holds them (3-D degree 1 with
-        // slab edges: 255 registers and a spill -> 213).  Mortar faces and
-        // block faces read as traces keep their own paths.  In 2-D
-        // (unrolled points) the per-point reads spill less.
-        constexpr bool FAR_REGS = D == 3;
-        const bool edge_m = FAR_REGS ? (!in_m && !mort_m && (ia > 0 || GM != GUARD_TRACE))
-                                     : (A == D - 1 && !in_m && ia > 0);
-        const bool edge_p = FAR_REGS ? (!in_p && !mort_p && (ia < N - 1 || GM != GUARD_TRACE))
-                                     : (A == D - 1 && !in_p && ia < N - 1);
-        constexpr int NBE = FAR_REGS ? NB : 1;
-        T nb[NV][NBE];
-        if constexpr (FAR_REGS) {
-            if (edge_m || edge_p) {
-                const int side = edge_m ? -1 : 1;
-                if (edge_m ? ia > 0 : ia < N - 1) { // slab edge: the neighbour cell
-                    const double *nk = g.us + base + side * stride;
+        const double sc = scale[A];
+        const SlabFaces<D> sf{N, rows, layer, g.inv_n};
+        double *const ext = lds + PITCH * (nslab + sf.first(A)); // 2 nE slots
+        const int nE = sf.count(A);
 #pragma unroll
-                    for (int v = 0; v < NV; ++v)
+        for (int v = 0; v < NV; ++v) {
+            double tp[NBF];
+            face_trace<D, P, A>(K[v], 1.0, tp);
 #pragma unroll
-                        for (int m = 0; m < NB; ++m) nb[v][m] = T(nk[v * sv + m * ncell]);
-                } else if (edge_m) { // (a link chosen at run time would go to scratch)
-                    far_poly<D, P, A, GM, NV, T>(g, K, leaf, -1, t, Lm, nb);
-                } else {
-                    far_poly<D, P, A, GM, NV, T>(g, K, leaf, +1, t, Lp, nb);
-                }
-            } else {
-#pragma unroll
-                for (int v = 0; v < NV; ++v)
-#pragma unroll
-                    for (int m = 0; m < NB; ++m) nb[v][m] = T(0);
-            }
+            for (int f = 0; f < NBF; ++f) lds[lc * PITCH + v * NBF + f] = tp[f];
         }
-        auto face_chunk_body = [&](auto cv) __attribute__((always_inline)) {
-            const int f0 = int(cv) * FCH;
-            // own traces of this chunk: + side to LDS, - side kept
-            T Tm[FCH][NV];
-            __syncthreads();
-#pragma unroll
-            for (int fi = 0; fi < FCH; ++fi)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    T e, o;
-                    trace_eo<D, P, T>(K[v], A, f0 + fi, e, o);
-                    lds[(v * FCH + fi) * nslab + lc] = e + o;
-                    Tm[fi][v] = e - o;
-                }
-            __syncthreads();
-            // flux on the - face: left state = the left neighbour's + trace
-            T Fm[FCH][NV];
-            if (in_m) {
-#pragma unroll
-                for (int fi = 0; fi < FCH; ++fi) {
-                    T TL[NV];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) TL[v] = lds[(v * FCH + fi) * nslab + lc - stride];
-                    num_flux<D, A, EQ, T>(gv, TL, Tm[fi], gamma, Fm[fi]);
-                }
-            } else if (edge_m) { // slab edge inside the leaf: the layer below
-#pragma unroll
-                for (int fi = 0; fi < FCH; ++fi) {
-                    T TL[NV];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        T e, o;
-                        if constexpr (FAR_REGS) trace_eo<D, P, T>(nb[v], A, f0 + fi, e, o);
-                        else trace_eo_mem<D, P, T>(g.us + base - stride + v * sv, ncell, A, f0 + fi, e, o);
-                        TL[v] = e + o;
-                    }
-                    num_flux<D, A, EQ, T>(gv, TL, Tm[fi], gamma, Fm[fi]);
-                }
-            } else if (!mort_m) {
-                T TL[FCH][NV];
-                far_traces<D, P, A, GM, FCH, NV, T>(g, K, leaf, -1, t, Lm, f0, TL);
-#pragma unroll
-                for (int fi = 0; fi < FCH; ++fi) num_flux<D, A, EQ, T>(gv, TL[fi], Tm[fi], gamma, Fm[fi]);
-            } else {
-#pragma unroll
-                for (int fi = 0; fi < FCH; ++fi)
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) Fm[fi][v] = T(0);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int fi = 0; fi < FCH; ++fi)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) lds[(v * FCH + fi) * nslab + lc] = Fm[fi][v];
-            __syncthreads();
-            T Fp[FCH][NV];
-            if (in_p) {
-#pragma unroll
-                for (int fi = 0; fi < FCH; ++fi)
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) Fp[fi][v] = lds[(v * FCH + fi) * nslab + lc + stride];
-            } else if (edge_p) { // slab edge inside the leaf: the layer above
-#pragma unroll
-                for (int fi = 0; fi < FCH; ++fi) {
-                    T TL[NV], TR[NV];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        T e, o;
-                        trace_eo<D, P, T>(K[v], A, f0 + fi, e, o);
-                        TL[v] = e + o;
-                        if constexpr (FAR_REGS) trace_eo<D, P, T>(nb[v], A, f0 + fi, e, o);
-                        else trace_eo_mem<D, P, T>(g.us + base + stride + v * sv, ncell, A, f0 + fi, e, o);
-                        TR[v] = e - o;
-                    }
-                    num_flux<D, A, EQ, T>(gv, TL, TR, gamma, Fp[fi]);
-                }
-            } else if (!mort_p) {
-                T TR[FCH][NV];
-                far_traces<D, P, A, GM, FCH, NV, T>(g, K, leaf, +1, t, Lp, f0, TR);
-#pragma unroll
-                for (int fi = 0; fi < FCH; ++fi) {
-                    T TL[NV];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        T e, o;
-                        trace_eo<D, P, T>(K[v], A, f0 + fi, e, o);
-                        TL[v] = e + o;
-                    }
-                    num_flux<D, A, EQ, T>(gv, TL, TR[fi], gamma, Fp[fi]);
-                }
-            } else {
-#pragma unroll
-                for (int fi = 0; fi < FCH; ++fi)
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) Fp[fi][v] = T(0);
-            }
-            // lift: R_m += s_a w phi_m(+1)/M_m ((-1)^{m_A} Phi_- - Phi_+)
-#pragma unroll
-            for (int fi = 0; fi < FCH; ++fi) {
-                const int F = f0 + fi;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const T dm = sc * Fm[fi][v], dp = sc * Fp[fi][v];
-                    const T even = dm - dp, odd = -(dm + dp);
-#pragma unroll
-                    for (int m = 0; m < NB; ++m) {
-                        const double c = kTab<D, P>.lift_f[A][F][m];
-                        if (use_entry<D, P>(c)) R[v][m] = fma(T(c), (kTab<D, P>.e[m][A] % 2 == 0) ? even : odd, R[v][m]);
-                    }
-                }
-            }
-        };
-        if constexpr (unroll_points<D, P>()) {
-            static_for<0, NF / FCH>(face_chunk_body);
-        } else {
+        bool mort_m = false, mort_p = false;
+        if (g.conservative) { // uniform: mortar on faces to finer leaves
+            const FaceLink Lm = g.links[leaf * 2 * D + 2 * A], Lp = g.links[leaf * 2 * D + 2 * A + 1];
+            mort_m = ia == 0 && Lm.type == dgamr::LINK_FINE;
+            mort_p = ia == N - 1 && Lp.type == dgamr::LINK_FINE;
+            if (mort_m) mortar_lift<D, P, A, EQ, double, false>(g, K, R, -1, Lm, face_t(ijk, A, N, D), sc);
+            if (mort_p) mortar_lift<D, P, A, EQ, double, false>(g, K, R, +1, Lp, face_t(ijk, A, N, D), sc);
+        }
+        __syncthreads();
+        // the - faces of all cells, then the + faces of the slab's last
+        // cells; alternate axes start from the other end of the workgroup so
+        // that the same waves do not take them all
+        const int e = A % 2 == 0 ? lc : nslab - 1 - lc;
 #pragma unroll 1
-            for (int ci = 0; ci < NF / FCH; ++ci) face_chunk_body(ci);
+        for (int pass = 0; pass < 2; ++pass) {
+            int side = 2 * pass - 1;
+            asm volatile("" : "+s"(side)); // one body for both passes
+            if (side > 0 && e >= nE) break;
+            const int own = side < 0 ? lc : sf.cell(A, 1, e); // whose + / - trace
+            // the neighbour's trace, and where the flux modes go
+            double *const nb = side < 0 && in_m ? lds + (lc - stride) * PITCH
+                                           : ext + (side < 0 ? sf.slot(A, lc) : nE + e) * PITCH;
+            double *const dst = side < 0 ? nb : lds + own * PITCH;
+            double Phi[NV][NBF];
+            face_flux<D, P, A, EQ>(
+                double(side), gamma, gv,
+                [&](int v, double *tr) __attribute__((always_inline)) {
+                    if (side < 0) {
+                        face_trace<D, P, A>(K[v], -1.0, tr);
+                    } else {
+#pragma unroll
+                        for (int f = 0; f < NBF; ++f) tr[f] = lds[own * PITCH + v * NBF + f];
+                    }
+                },
+                [&](int v, int f) __attribute__((always_inline)) { return nb[v * NBF + f]; }, Phi);
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int f = 0; f < NBF; ++f) dst[v * NBF + f] = Phi[v][f];
+            if (side < 0 && !mort_m) lift<D, P, A, EQ>(Phi, -1, sc, R);
+        }
+        __syncthreads();
+        if (!mort_p) {
+            double Phi[NV][NBF];
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int f = 0; f < NBF; ++f) Phi[v][f] = lds[lc * PITCH + v * NBF + f];
+            lift<D, P, A, EQ>(Phi, +1, sc, R);
         }
     });
 
@@ -826,12 +997,7 @@ __device__ __forceinline__ void stage_item(const StageArgs &g, int rows, int ite
 #pragma unroll
         for (int v = 0; v < NV; ++v)
 #pragma unroll
-            for (int m = 0; m < NB; ++m) plane(g.out64, v, m)[uc] = double(R[v][m]);
-    } else if constexpr (OM == OUT_RES32) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v)
-#pragma unroll
-            for (int m = 0; m < NB; ++m) plane(g.out32, v, m)[uc] = float(R[v][m]);
+            for (int m = 0; m < NB; ++m) plane(g.out64, v, m)[uc] = R[v][m] * kTab<D, P>.inv_mass[m];
     } else {
         double dt;
         if (g.rate_in) {
@@ -843,27 +1009,11 @@ __device__ __forceinline__ void stage_item(const StageArgs &g, int rows, int ite
         }
         if (g.rate_clear && item == 0 && threadIdx.x == 0) *g.rate_clear = 0ULL;
         const double a = g.rk_a, b = g.rk_b;
-        // FP64 update; the FP32 path re-reads U_s at full precision
         double Kn[NV][NB];
-        if constexpr (std::is_same<T, double>::value) {
 #pragma unroll
-            for (int v = 0; v < NV; ++v)
+        for (int v = 0; v < NV; ++v)
 #pragma unroll
-                for (int m = 0; m < NB; ++m) Kn[v][m] = b * (K[v][m] + dt * R[v][m]);
-        } else if (b != 0.0) {
-            // FP32 path: U_s again at full precision; inside a (uniform)
-            // branch so that its loads are issued here, not held in
-            // registers through the residual
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-#pragma unroll
-                for (int m = 0; m < NB; ++m) Kn[v][m] = b * (plane(g.us, v, m)[uc] + dt * double(R[v][m]));
-        } else {
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-#pragma unroll
-                for (int m = 0; m < NB; ++m) Kn[v][m] = 0.0;
-        }
+            for (int m = 0; m < NB; ++m) Kn[v][m] = b * fma(dt * kTab<D, P>.inv_mass[m], R[v][m], K[v][m]);
         // stages 2 and 3 add the RK base state; a uniform branch keeps its
         // loads here, after the residual, instead of live through it
         if (a != 0.0) {
@@ -892,11 +1042,24 @@ __device__ __forceinline__ void stage_item(const StageArgs &g, int rows, int ite
 #pragma unroll
                 for (int a2 = 0; a2 < D; ++a2) rate += (fabs(U[1 + a2] * rinv) + cs) / g.geo[leaf].h[a2];
             }
-            block_max_to(rate, lds_d, g.rate_out);
+            block_max_to(rate, lds, g.rate_out);
         }
     }
 }
 
+// Whether the stage item contracts axis by axis: FP64, 2-D and 3-D to degree
+// 1.  From degree 2 in 3-D one thread cannot hold the state, the residual
+// and a face's traces and fluxes (16^3 roots, degree 2: 15.2 ms per two steps
+// point by point, 16.2 axis by axis with 440 bytes of spills)
+template <int D, int P, typename T>
+constexpr bool by_axis() { return sizeof(T) == 8 && (D == 2 || P <= 1); }
+
+// the item with the contractions point by point (kernels_points.hpp)
+template <int D, int P, int GM, int OM, bool LIM, typename T, int EQ, bool MF>
+__device__ __forceinline__ void stage_item_points(const StageArgs &g, int rows, int item, int total);
+
+// T: the arithmetic of the residual, double or float (the state, the stage
+// update, the limiter and the CFL rate are FP64).
 // The stage kernel: one workgroup per (leaf, slab) work item, or (PERSIST,
 // a grid smaller than the item count) each workgroup walks the items with
 // a stride of the grid size.  With a grid that is a
@@ -908,11 +1071,17 @@ __global__ __launch_bounds__((stage_threads<D, P, T>()), (stage_min_waves<D, P, 
                                                                                                      int rows)
 {
     const int total = g.nleaves * (g.N / rows);
+    auto run = [&](int item) __attribute__((always_inline)) {
+        if constexpr (by_axis<D, P, T>()) stage_item<D, P, GM, OM, LIM, EQ>(g, rows, item, total);
+        else stage_item_points<D, P, GM, OM, LIM, T, EQ, MF>(g, rows, item, total);
+    };
     if constexpr (PERSIST) {
-        for (int item = blockIdx.x; item < total; item += gridDim.x)
-            stage_item<D, P, GM, OM, LIM, T, EQ, MF>(g, rows, item, total);
+        for (int item = blockIdx.x; item < total; item += gridDim.x) {
+            run(item);
+            if constexpr (by_axis<D, P, T>()) __syncthreads(); // the next item reuses the LDS
+        }
     } else { // one item per workgroup: no loop to hold values across items
-        stage_item<D, P, GM, OM, LIM, T, EQ, MF>(g, rows, blockIdx.x, total);
+        run(blockIdx.x);
     }
 }
 
