@@ -221,10 +221,9 @@ int dgamr_get_time(const dgamr_forest *f, double *t);
  * guard fill, the residual and the stage update (and the positivity limiter
  * when the forest asks for it).  The far side of every block face is
  * computed inside the stage kernel straight from the neighbours' cells (same
- * values as dgamr_fill_guardcells), except where a fill kernel writes into
- * the work buffer before each stage: guard traces for the 3-D
- * lane-per-(cell, variable) kernel, and guard coefficients on forests with
- * rotated root frames or bilinear / trilinear roots.  Asynchronous;
+ * values as dgamr_fill_guardcells), except on forests with rotated root
+ * frames or bilinear / trilinear roots, where a fill kernel writes guard
+ * coefficients into the work buffer before each stage.  Asynchronous;
  * captures into a HIP graph.  Diffusion
  * forests (cfl > 0 required; dt computed on the host from the forest's
  * finest cells and written to dt_dev): per stage the guard fill of
@@ -301,9 +300,9 @@ int dgamr_check_state(dgamr_forest *f, const double *u, int64_t *bad, void *work
  *   DGAMR_TUNE_STAGE_VARIANT: stage kernel, -1 automatic (default),
  *     0 one lane per (cell, variable), 1 one thread per cell.  2-D: variant
  *     0 in row slabs for latency-bound small forests, 1 for throughput on
- *     large forests.  3-D (fused FP64 stage without the limiter or mortar
- *     faces; other forests always run variant 1): variant 0 in slabs of
- *     layers, automatic at degree 3;
+ *     large forests.  3-D (FP64 without the limiter or mortar faces; other
+ *     forests always run variant 1): variant 0 in slabs of layers, automatic
+ *     from degree 2;
  *   DGAMR_TUNE_VAR_SPLIT_MAX_CELLS: the automatic 2-D choice uses variant 0
  *     up to this many cells (default 131072);
  *   DGAMR_TUNE_SLAB_ROWS: layers of the block's last axis per stage

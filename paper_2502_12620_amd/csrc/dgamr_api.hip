@@ -89,13 +89,12 @@ int upload(dgamr_forest *f)
     return DGAMR_OK;
 }
 
-// guard cells of every block face, as coefficients or (traces) as their
-// values at the face points
-int launch_fill(dgamr_forest *f, const double *u, double *guard, bool traces, hipStream_t s)
+// guard cells of every block face
+int launch_fill(dgamr_forest *f, const double *u, double *guard, hipStream_t s)
 {
     int nf = 2 * f->topo.dim();
     dgk::FillArgs a{u,       guard, f->d_links, f->d_plans, nullptr, f->topo.n() * nf, f->topo.desc().n_cell,
-                    traces ? 1 : 0, f->topo.mapped() ? 1 : 0};
+                    f->topo.mapped() ? 1 : 0};
     if (a.nfaces == 0) return DGAMR_OK;
     return dispatch(f->topo.dim(), f->topo.desc().degree, [&](auto D, auto P) -> int {
         HIP_TRY((dgk::launch_fill<D, P>(a, nfc_of(f), s, nv_of(f))));
@@ -106,9 +105,9 @@ int launch_fill(dgamr_forest *f, const double *u, double *guard, bool traces, hi
 int stage_variant(const dgamr_forest *f)
 {
     if (f->stage_variant >= 0) return f->stage_variant;
-    // 3-D: one lane per (cell, variable) at degree 3, where one thread per
-    // cell runs out of registers; one thread per cell below (measured)
-    if (f->topo.dim() == 3) return f->topo.desc().degree >= 3 ? 0 : 1;
+    // 3-D: one lane per (cell, variable) from degree 2, where one thread's
+    // state and residual leave one wave per SIMD; one thread per cell below
+    if (f->topo.dim() == 3) return f->topo.desc().degree >= 2 ? 0 : 1;
     return long(f->topo.n()) * ncell_of(f) <= f->var_split_max_cells ? 0 : 1;
 }
 
@@ -119,16 +118,6 @@ dgk::StageShape stage_shape(const dgamr_forest *f)
     sh.rows = f->slab_rows;
     sh.mfma = f->mfma;
     return sh;
-}
-
-// the fused stage of this forest reads guard traces (the 3-D lane kernel)
-bool fused_reads_traces(const dgamr_forest *f)
-{
-    if (f->topo.unfused()) return false;
-    return dgk::stage_reads_traces(f->topo.dim(), stage_shape(f), f->topo.desc().limiter == DGAMR_LIMITER_POSITIVITY,
-                                   f->topo.desc().precision == DGAMR_FP32,
-                                   f->topo.desc().hanging == DGAMR_HANG_CONSERVATIVE, f->topo.advection(),
-                                   f->topo.desc().n_cell);
 }
 
 int launch_stage(dgamr_forest *f, dgk::StageArgs a, int gm, int om, hipStream_t s, bool lim = false)
@@ -303,7 +292,7 @@ int step_diffusion(dgamr_forest *f, double cfl, double *u, const Work &w, double
     const double *us = u;
     double *outs[3] = {w.u1, w.u2, u};
     for (int st = 0; st < 3; ++st) {
-        CHECK(launch_fill(f, us, w.guard, false, s));
+        CHECK(launch_fill(f, us, w.guard, s));
         CHECK(launch_ipdg(f, us, u, w.guard, outs[st], dt_dev, A[st], B[st], f->time + C[st] * dt, dgk::OUT_RK, s));
         us = outs[st];
     }
@@ -439,7 +428,7 @@ int dgamr_fill_guardcells(dgamr_forest *f, const double *u, double *guard, hipSt
     CHECK(check_ptr(f, "forest"));
     CHECK(check_ptr(u, "u"));
     CHECK(check_ptr(guard, "guard"));
-    return launch_fill(f, u, guard, false, stream);
+    return launch_fill(f, u, guard, stream);
 }
 
 int dgamr_dg_residual(dgamr_forest *f, const double *u, const double *guard, void *r, hipStream_t stream)
@@ -524,7 +513,7 @@ int prof_end(dgamr_forest *f, hipStream_t stream, hipEvent_t e1)
 }
 
 // One SSP-RK3 step as three fused stage launches (far side of block faces
-// inline, or from guard traces for the 3-D lane kernel; limiter fused).  rate_in / rate_clear / rate_out select the CFL
+// inline; limiter fused).  rate_in / rate_clear / rate_out select the CFL
 // time step folded into the stages (see StageArgs).
 int run_step(dgamr_forest *f, double cfl, double *u, const Work &w, double *dt_dev,
              const unsigned long long *rate_in, unsigned long long *rate_clear, unsigned long long *rate_out,
@@ -542,7 +531,7 @@ int run_step(dgamr_forest *f, double cfl, double *u, const Work &w, double *dt_d
         for (int s = 0; s < 3; ++s) {
             hipEvent_t e1;
             CHECK(prof_begin(f, stream, e1));
-            CHECK(launch_fill(f, us, w.guard, false, stream));
+            CHECK(launch_fill(f, us, w.guard, stream));
             dgk::MappedArgs a = mapped_args(f, us, u, w.guard, outs[s], dt_dev, A[s], B[s]);
             CHECK(dispatch_mapped(f, [&](auto D, auto P) -> int {
                 HIP_TRY((dgk::launch_mapped<D, P>(a, eq, dgk::OUT_RK, lim, stream)));
@@ -561,7 +550,7 @@ int run_step(dgamr_forest *f, double cfl, double *u, const Work &w, double *dt_d
         for (int s = 0; s < 3; ++s) {
             hipEvent_t e1;
             CHECK(prof_begin(f, stream, e1));
-            CHECK(launch_fill(f, us, w.guard, false, stream));
+            CHECK(launch_fill(f, us, w.guard, stream));
             dgk::StageArgs a{};
             a.us = us;
             a.un = u;
@@ -591,17 +580,9 @@ int run_step(dgamr_forest *f, double cfl, double *u, const Work &w, double *dt_d
         a.rate_clear = s == 0 ? rate_clear : nullptr;
         a.dt_out = dt_dev;
         a.rate_out = s == 2 ? rate_out : nullptr;
-        // the 3-D lane kernel reads the far side of every block face as
-        // traces from the guard buffer; the other stage kernels compute it
-        // inline
-        const bool guard3 = fused_reads_traces(f);
-        if (guard3) {
-            a.guard = w.guard;
-            CHECK(launch_fill(f, us, w.guard, true, stream));
-        }
         hipEvent_t e1;
         CHECK(prof_begin(f, stream, e1));
-        CHECK(launch_stage(f, a, guard3 ? dgk::GUARD_TRACE : dgk::GUARD_INLINE, dgk::OUT_RK, stream, lim));
+        CHECK(launch_stage(f, a, dgk::GUARD_INLINE, dgk::OUT_RK, stream, lim));
         CHECK(prof_end(f, stream, e1));
         us = outs[s];
     }
@@ -848,7 +829,7 @@ int dgamr_indicator(dgamr_forest *f, const double *u, double *eta_dev, void *wor
     CHECK(check_ptr(eta_dev, "eta_dev"));
     CHECK(check_ptr(work, "work"));
     Work w = carve(f, work);
-    CHECK(launch_fill(f, u, w.guard, false, stream));
+    CHECK(launch_fill(f, u, w.guard, stream));
     int n = f->topo.n();
     if (n == 0) return DGAMR_OK;
     if (f->topo.scalar() && f->topo.dim() == 2)

@@ -58,25 +58,36 @@ hipError_t launch_stage_2v(const StageArgs &a, int gm, int om, hipStream_t s, in
     return hipGetLastError();
 }
 
-// 3-D fused FP64 stage with one lane per (cell, variable)
+// 3-D FP64 residual or fused stage with one lane per (cell, variable)
 template <int P>
-hipError_t launch_stage_3v(const StageArgs &a, hipStream_t s, int rows_req)
+hipError_t launch_stage_3v(const StageArgs &args, int gm, int om, hipStream_t s, int rows_req)
 {
-    const int N = a.N, layer = N * N;
+    StageArgs a = args;
+    a.inv_n = unsigned((65536 + a.N - 1) / a.N);
+    const int N = a.N;
     int rows = rows_req;
     if (rows > 0) {
         if (!rows_ok_3v(N, rows)) return hipErrorInvalidValue;
     } else {
-        rows = rows_3v(N);
-        if (rows == 0) return hipErrorInvalidValue;
-        // small forests: thinner slabs until every compute unit has work
-        while (rows % 2 == 0 && rows_ok_3v(N, rows / 2) && long(a.nleaves) * (N / rows) < 256) rows /= 2;
+        // whole leaves, in thinner slabs until every compute unit has work
+        rows = N;
+        while (rows % 2 == 0 && long(a.nleaves) * (N / rows) < 1024) rows /= 2;
     }
-    const int nslab = rows * layer;
-    const int waves = (nslab + kCells3v - 1) / kCells3v;
-    const size_t lds = sizeof(double) * size_t(face_chunk_3v<P>()) * nslab * 5;
-    const dim3 grid(unsigned(long(a.nleaves) * (N / rows))), block(64 * waves);
-    hipLaunchKernelGGL((k_stage3v<P>), grid, block, lds, s, a, rows);
+    const int waves = (N * N + N + kCells3v - 1) / kCells3v;
+    int group = 1; // items per workgroup: whole fours of waves
+    while (waves * group % 4 != 0) ++group;
+    const int lds_item = waves * 5 * kCells3v * kRec3v + (N * N + 4 * N) * ((5 * face_modes<3, P>()) | 1);
+    const size_t lds = sizeof(double) * size_t(lds_item) * group;
+    const long items = long(a.nleaves) * (N / rows);
+    const dim3 grid(unsigned((items + group - 1) / group)), block(64 * waves * group);
+    if (gm == GUARD_INLINE && om == OUT_RK)
+        hipLaunchKernelGGL((k_stage3v<P, GUARD_INLINE, OUT_RK>), grid, block, lds, s, a, rows, waves, group, lds_item);
+    else if (gm == GUARD_BUFFER && om == OUT_RK)
+        hipLaunchKernelGGL((k_stage3v<P, GUARD_BUFFER, OUT_RK>), grid, block, lds, s, a, rows, waves, group, lds_item);
+    else if (gm == GUARD_BUFFER && om == OUT_RES64)
+        hipLaunchKernelGGL((k_stage3v<P, GUARD_BUFFER, OUT_RES64>), grid, block, lds, s, a, rows, waves, group, lds_item);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
@@ -227,12 +238,7 @@ hipError_t launch_stage(const StageArgs &a, int gm, int om, bool lim, bool fp32,
         // thread per cell (variant 1) or needs the limiter
         if (!lim && (sh.variant == 0 || om != OUT_RK)) return launch_stage_2v<P>(a, gm, om, s, sh.rows);
     } else {
-        // the fused stage reading guard traces is the lane kernel (the
-        // caller filled the traces because stage_reads_traces holds)
-        if (gm == GUARD_TRACE && om == OUT_RK) {
-            if (!stage_reads_traces(3, sh, lim, false, a.conservative != 0, false, a.N)) return hipErrorInvalidValue;
-            return launch_stage_3v<P>(a, s, sh.rows);
-        }
+        if (lanes_3d(sh, lim, false, a.conservative != 0, false, a.N)) return launch_stage_3v<P>(a, gm, om, s, sh.rows);
     }
     return launch_stage_cell<D, P, double>(a, gm, om, lim, sh, s);
 }

@@ -218,11 +218,9 @@ __device__ __forceinline__ void rusanov(const T *UL, const T *UR, T gamma, T *Ph
 // ------------------------------------------------------------------ argument blocks
 enum GuardMode : int {
     GUARD_BUFFER = 0, // every block face from the guard buffer (coefficients)
-    GUARD_INLINE = 1, // every block face straight from the neighbours' cells:
+    GUARD_INLINE = 1  // every block face straight from the neighbours' cells:
                       // copy, split of the coarser cell or combine of the
                       // finer cells computed on the fly (no guard buffer)
-    GUARD_TRACE = 2   // every block face from the guard buffer holding the
-                      // guard cells' traces at the face points
 };
 enum OutMode : int { OUT_RES64 = 0, OUT_RES32 = 1, OUT_RK = 2 };
 
@@ -341,8 +339,6 @@ struct FillArgs {
     const int *work;   // leaves whose 2d faces are filled (null: all leaves)
     int nfaces;        // number of faces to fill (2d per listed leaf)
     int N;
-    int traces;        // 0: guard coefficients G[leaf][face][var][mode][t];
-                       // 1: their traces on the face, G[leaf][face][var][point][t]
     int global_vectors; // 1: momentum along the global axes (bilinear / trilinear
                         // roots): across rotated frames only the coordinates turn
 };

@@ -1088,11 +1088,11 @@ __global__ __launch_bounds__((stage_threads<D, P, T>()), (stage_min_waves<D, P, 
 // ------------------------------------------------------------------ guard fill
 // One thread per guard cell (leaf, face, t): Eq. 15 copy, Eq. 16 split of the
 // coarser neighbour cell, Eq. 17 combine of the 2^d finer cells, outflow
-// mirror K_m (-1)^{m_axis}; written as coefficients or as face traces.
+// mirror K_m (-1)^{m_axis}.
 template <int D, int P, int NV = D + 2>
 __global__ __launch_bounds__(256) void k_fill(FillArgs g)
 {
-    constexpr int NB = Tab<D, P>::NB, NF = Tab<D, P>::NF;
+    constexpr int NB = Tab<D, P>::NB;
     const int N = g.N, ncell = D == 2 ? N * N : N * N * N, nfc = D == 2 ? N : N * N;
     const long gid = long(blockIdx.x) * blockDim.x + threadIdx.x;
     if (gid >= long(g.nfaces) * nfc) return;
@@ -1102,27 +1102,11 @@ __global__ __launch_bounds__(256) void k_fill(FillArgs g)
     const int a = face / 2, side = (face & 1) ? 1 : -1;
     const FaceLink L = g.links[lf];
     const long sv = long(NB) * ncell;
-    // one variable of the guard cell -> coefficients, or its values at the
-    // face points (the guard cell touches the face with its -side side)
+    // one variable of the guard cell
     auto emit = [&](int v, const double *gk) __attribute__((always_inline)) {
-        if (g.traces) {
-            double *out = g.guard + (long(lf) * NV * NF) * nfc + t;
-            for (int f = 0; f < NF; ++f) {
-                double s = 0.0;
+        double *out = g.guard + (long(lf) * NV * NB) * nfc + t;
 #pragma unroll
-                for (int m = 0; m < NB; ++m) {
-                    const int ex = kTab<D, P>.e[m][0] * (a == 0) + kTab<D, P>.e[m][1] * (a == 1) +
-                                   kTab<D, P>.e[m][2] * (a == 2);
-                    const double c = kTab<D, P>.phi_f[a][f][m];
-                    s = fma((side > 0 && (ex % 2)) ? -c : c, gk[m], s);
-                }
-                out[(v * NF + f) * nfc] = s;
-            }
-        } else {
-            double *out = g.guard + (long(lf) * NV * NB) * nfc + t;
-#pragma unroll
-            for (int m = 0; m < NB; ++m) out[(v * NB + m) * nfc] = gk[m];
-        }
+        for (int m = 0; m < NB; ++m) out[(v * NB + m) * nfc] = gk[m];
     };
     if (L.rot > 0) {
         // a neighbour root of another frame (Sec. 3.5): copy, split or combine

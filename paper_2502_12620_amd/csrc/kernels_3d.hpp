@@ -4,16 +4,20 @@
 // (lanes 60..63 repeat the last cell's lanes and store nothing).  Each lane
 // keeps only its variable's coefficients and residual, so a cell's state
 // and residual take 4 N_b registers per lane instead of 20 N_b in one
-// thread; the full state at a point, needed by the Euler and Rusanov
-// fluxes, is gathered from the cell's five lanes with ds_bpermute.  A
-// workgroup covers a slab of layers (along z) of one leaf; faces inside the
-// slab exchange traces and fluxes through LDS in chunks of face points,
-// faces on a slab edge inside the leaf are recomputed from the adjacent
-// layer, and leaf faces read the far side as traces from the guard buffer
-// (the fill kernel writes them before each stage: copy, split, combine,
-// outflow mirror).  Runs the fused RK stage in FP64 for the Euler
-// equations without the limiter and without mortar faces; everything else
-// takes the thread-per-cell kernel.
+// thread.  The Euler and Rusanov fluxes need all five variables of a point:
+// the lanes of a cell write five points' values to LDS records, each lane
+// then computes the flux of one of the five points, and the lanes read their
+// variable back, so no flux is computed twice.
+//
+// A workgroup covers a slab of layers of one leaf, one layer at a time along
+// z.  A face between two layers needs no exchange (the same lanes hold both
+// cells: the next layer is loaded while the current one is computed); x and
+// y faces go through LDS as face modes as in the thread-per-cell kernel, the
+// + faces of a layer's last cells computed by the cell slots that the
+// layer's N^2 cells leave free (N = 8: 72 slots in 6 waves, 64 cells and 8
+// faces).  Runs the fused RK stage in FP64 for the Euler equations without
+// the limiter and without mortar faces; everything else takes the
+// thread-per-cell kernel.
 #pragma once
 
 #include "kernels_2d.hpp"
@@ -21,272 +25,445 @@
 
 namespace dgk {
 
-// face points exchanged through LDS at once
-template <int P>
-constexpr int face_chunk_3v() { return P == 0 ? 1 : (P == 1 ? 4 : (P == 2 ? 3 : 2)); }
-
-// value of x held by the lane at byte address addr (4 * lane)
-__device__ __forceinline__ double lane_get(double x, int addr)
-{
-    const int lo = __builtin_amdgcn_ds_bpermute(addr, __double2loint(x));
-    const int hi = __builtin_amdgcn_ds_bpermute(addr, __double2hiint(x));
-    return __hiloint2double(hi, lo);
-}
-
-// full state of the cell from its five lanes' values (addr0: byte address
-// of the cell's first lane)
-__device__ __forceinline__ void cell_state5(double x, int addr0, double *U)
-{
-#pragma unroll
-    for (int j = 0; j < 5; ++j) U[j] = lane_get(x, addr0 + 4 * j);
-}
-
-// Rusanov flux (Eq. 5, dissipative sign, +e_A direction) of this lane's
-// variable between left value tl and right value tr
-template <int A>
-__device__ __forceinline__ double rusanov_5(double tl, double tr, int addr0, double gamma, double isM, double isE)
-{
-    double L[5], R[5];
-    cell_state5(tl, addr0, L);
-    cell_state5(tr, addr0, R);
-    const double gm1 = gamma - 1.0;
-    const double rl = recip(L[0]), rr = recip(R[0]);
-    const double pl = pressure_r<3>(L, gm1, rl), pr = pressure_r<3>(R, gm1, rr);
-    const double ul = L[1 + A] * rl, ur = R[1 + A] * rr;
-    const double al = fabs(ul) + sqrt_nn(gamma * pl * rl), ar = fabs(ur) + sqrt_nn(gamma * pr * rr);
-    const double alpha = al > ar ? al : ar;
-    const double fl = flux_v<A>(tl, ul, pl, isM, isE), fr = flux_v<A>(tr, ur, pr, isM, isE);
-    return 0.5 * ((fl + fr) - alpha * (tr - tl));
-}
-
-// even / odd parts (in the normal mode index) of the trace at face point f
-// of axis A (a constant after unrolling: zero table entries drop out)
-template <int P, int A>
-__device__ __forceinline__ void trace3(const double *K, int f, double &e, double &o)
-{
-    e = 0.0;
-    o = 0.0;
-#pragma unroll
-    for (int m = 0; m < Tab<3, P>::NB; ++m) {
-        const double c = kTab<3, P>.phi_f[A][f][m];
-        if (c != 0.0) {
-            if (kTab<3, P>.e[m][A] % 2 == 0) e = fma(c, K[m], e);
-            else o = fma(c, K[m], o);
-        }
-    }
-}
-
-// An empty asm that takes and returns x: everything x depends on is computed
-// before it, and a scheduling barrier after it keeps later work below.
-// Without these the scheduler hoists the lane gathers and the table
-// constants of every quadrature point ahead and holds them in registers.
+// An empty asm that takes and returns x: what x depends on is computed before
+// it.  Without it the compiler sinks the residual's contractions to the
+// stage update and keeps every flux of the volume integral until then.
 #define DG_PIN(x) asm volatile("" : "+v"(x))
 
-// The point loops are unrolled at every degree (table entries become
-// constants).  At degree 3 loops over the tables read with scalar loads
-// spill less (92 against 260 bytes per lane) but wait on a scalar load at
-// every point: 2.13 ms against 1.30 ms per stage on 8^3 roots of 8^3 cells.
+// doubles of one point's LDS record: five variables of the own and of the
+// neighbour's state in, the flux out; odd, to spread the records over the banks
+constexpr int kRec3v = 11;
 
-// grid: one workgroup per (leaf, slab of `rows` layers); block: 64 lanes per
-// 12 cells of the slab (rows * N * N <= 144 cells)
+// waves per SIMD the register budget is cut for
 template <int P>
-__global__ __launch_bounds__(kThreads3v) void k_stage3v(StageArgs g, int rows)
+constexpr int waves_3v() { return P <= 1 ? 4 : 3; }
+
+// Euler flux of a point's five variables: the lanes of a cell exchange the
+// values of up to five points through the wave's LDS records (rec: the
+// record of the cell's point 0; own: this lane's own record).
+struct Lanes3 {
+    double *rec, *own;
+    int v;
+    __device__ __forceinline__ void put(int o, int slot, double x) const { rec[o * kRec3v + slot * 5 + v] = x; }
+    __device__ __forceinline__ double get(int o) const { return rec[o * kRec3v + v]; }
+};
+
+// Volume integral of this lane's variable: R_m += int F_a dphi_m/dx_a.  sc:
+// 2/h_a; isE, isM: 1 on the lane of the energy / the momentum along a.
+template <int P>
+__device__ __forceinline__ void volume_3v(const double *K, double *R, const Lanes3 &ln, const double *sc, double gm1,
+                                          double isE, const double *isM)
 {
-    constexpr int NV = 5, NB = Tab<3, P>::NB, NQ = Tab<3, P>::NQ, NF = Tab<3, P>::NF;
-    constexpr int FCH = face_chunk_3v<P>();
-    static_assert(NF % FCH == 0, "face points come in whole chunks");
-    extern __shared__ double lds[];
-    const int N = g.N, layer = N * N, ncell = layer * N;
-    const int slabs = N / rows;
-    const int wg = xcd_leaf(blockIdx.x, g.nleaves * slabs);
-    const int li = wg / slabs, k0 = (wg % slabs) * rows;
-    const int leaf = g.work ? g.work[li] : li; // listed leaves of a pool, or all
-    const int nslab = rows * layer;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int lv = lane < 5 * kCells3v ? lane : lane - 5; // lanes 60..63 repeat lanes 55..58
-    const int cw = lv / 5, v = lv - 5 * cw;
-    const int addr0 = 4 * 5 * cw;                          // byte address of the cell's first lane
-    const int lraw = wave * kCells3v + cw;
-    const bool live = lane < 5 * kCells3v && lraw < nslab; // slots past the slab repeat its last cell
-    const int lc = lraw < nslab ? lraw : nslab - 1;
-    const int cell = lc + k0 * layer;
-    const int ijk[3] = {cell % N, (cell / N) % N, cell / layer};
-    const double isE = v == 4 ? 1.0 : 0.0;
-    const double scale[3] = {g.geo[leaf].scale[0], g.geo[leaf].scale[1], g.geo[leaf].scale[2]};
-    const long sv = long(NB) * ncell;
-    const long vbase = long(leaf) * NV * sv + v * sv; // this variable's planes in this leaf
-    const long idx0 = vbase + cell;
-
-    double K[NB], R[NB];
+    constexpr int NB = Tab<3, P>::NB, NQ = Tab<3, P>::NQ, Q = P + 1, NB2 = Q * (Q + 1) / 2;
+    double C[NB2], row[Q], rx[P], ry[P], rz[P];
+    const double cm[3] = {isM[0] * sc[0], isM[1] * sc[1], isM[2] * sc[2]};
+    static_for<0, (NQ + 4) / 5>([&](auto gv) __attribute__((always_inline)) {
+        double val[5];
+        static_for<0, 5>([&](auto ov) __attribute__((always_inline)) {
+            constexpr int o = ov, q = 5 * decltype(gv)::value + o;
+            if constexpr (q < NQ) {
+                constexpr int qx = q % Q, qy = (q / Q) % Q, qz = q / (Q * Q);
+                if constexpr (qx == 0 && qy == 0) // the polynomial on this plane
 #pragma unroll
-    for (int m = 0; m < NB; ++m) {
-        K[m] = g.us[idx0 + long(m) * ncell];
-        R[m] = 0.0;
-    }
-
-    // ---- volume integral
-    const double gm1 = g.gamma - 1.0;
-    auto vol_point = [&](auto qv) __attribute__((always_inline)) {
-        const int q = qv;
-        double s = 0.0;
+                    for (int m = 0; m < NB; ++m) {
+                        const int f = mode2(kTab<3, P>.e[m][0], kTab<3, P>.e[m][1]), k = kTab<3, P>.e[m][2];
+                        const double c = kRule<P>.val[qz][k];
+                        if (k == 0) C[f] = K[m];
+                        else if (c != 0.0) C[f] = fma(c, K[m], C[f]);
+                    }
+                if constexpr (qx == 0) // on this row
 #pragma unroll
-        for (int m = 0; m < NB; ++m) {
-            const double c = kTab<3, P>.phi_v[q][m];
-            if (c != 0.0) s = fma(c, K[m], s);
-        }
-        double U[5];
-        cell_state5(s, addr0, U);
-        const double rinv = recip(U[0]);
-        const double p = pressure_r<3>(U, gm1, rinv);
-        static_for<0, 3>([&](auto Ai) __attribute__((always_inline)) {
-            constexpr int A = Ai;
-            const double isM = v == 1 + A ? 1.0 : 0.0;
-            const double F = scale[A] * flux_v<A>(s, U[1 + A] * rinv, p, isM, isE);
+                    for (int i = 0; i < Q; ++i) {
+                        row[i] = C[mode2(i, 0)];
 #pragma unroll
-            for (int m = 0; m < NB; ++m) {
-                const double c = kTab<3, P>.dproj[A][q][m];
-                // a mode of degree 0 along A has no derivative along A
-                if (kTab<3, P>.e[m][A] != 0 && c != 0.0) R[m] = fma(c, F, R[m]);
+                        for (int j = 1; i + j < Q; ++j) {
+                            const double c = kRule<P>.val[qy][j];
+                            if (c != 0.0) row[i] = fma(c, C[mode2(i, j)], row[i]);
+                        }
+                    }
+                double s = row[0];
+#pragma unroll
+                for (int i = 1; i < Q; ++i) {
+                    const double c = kRule<P>.val[qx][i];
+                    if (c != 0.0) s = fma(c, row[i], s);
+                }
+                val[o] = s;
+                ln.put(o, 0, s);
             }
         });
+        wave_lds_sync();
+        { // this lane's point: velocities times 2/h_a, and the pressure
+            double U[5];
 #pragma unroll
-        for (int m = 0; m < NB; ++m) DG_PIN(R[m]);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    static_for<0, NQ>(vol_point);
-
-    // ---- surface integrals, one axis at a time; LDS slot of (chunk point,
-    // slab cell, variable)
-    auto slot = [&](int fi, int c) { return (fi * nslab + c) * NV + v; };
-    static_for<0, 3>([&](auto Ai) __attribute__((always_inline)) {
-        constexpr int A = Ai;
-        const double isM = v == 1 + A ? 1.0 : 0.0;
-        const int stride = A == 0 ? 1 : (A == 1 ? N : layer);
-        const int ia = ijk[A];
-        const bool in_m = A == 2 ? ia > k0 : ia > 0;            // - neighbour inside the slab
-        const bool in_p = A == 2 ? ia < k0 + rows - 1 : ia < N - 1;
-        const int t = face_t(ijk, A, N, 3);
-        const double sc = scale[A];
-        // far-side traces of the leaf faces: G[leaf][face][var][point][t]
-        const double *gt_m = g.guard + ((long(leaf) * 6 + 2 * A) * NV * NF + long(v) * NF) * layer + t;
-        const double *gt_p = g.guard + ((long(leaf) * 6 + 2 * A + 1) * NV * NF + long(v) * NF) * layer + t;
-        // slabs hold whole layers of at least two rows, so only a z face
-        // can be a slab edge, and a cell has at most one: its neighbour's
-        // coefficients across it, read once
-        const bool edge_m = A == 2 && !in_m && ia > 0, edge_p = A == 2 && !in_p && ia < N - 1;
-        double nb[NB];
-        if (A == 2 && (edge_m || edge_p)) {
-            const double *nk = g.us + idx0 + (edge_m ? -stride : stride);
+            for (int b = 0; b < 5; ++b) U[b] = ln.own[b];
+            const double rinv = recip(U[0]);
+            const double p = pressure_r<3>(U, gm1, rinv);
 #pragma unroll
-            for (int m = 0; m < NB; ++m) nb[m] = nk[long(m) * ncell];
-        } else {
-#pragma unroll
-            for (int m = 0; m < NB; ++m) nb[m] = 0.0;
+            for (int a = 0; a < 3; ++a) ln.own[a] = U[1 + a] * (rinv * sc[a]);
+            ln.own[3] = p;
         }
-        auto chunk = [&](auto cv) __attribute__((always_inline)) {
-            const int f0 = int(cv) * FCH;
-            double Tm[FCH], Fm[FCH], Fp[FCH];
-            __syncthreads();
+        wave_lds_sync();
+        static_for<0, 5>([&](auto ov) __attribute__((always_inline)) {
+            constexpr int o = ov, q = 5 * decltype(gv)::value + o;
+            if constexpr (q < NQ) {
+                constexpr int qx = q % Q, qy = (q / Q) % Q, qz = q / (Q * Q);
+                const double p = ln.rec[o * kRec3v + 3];
+                static_for<0, 3>([&](auto Ai) __attribute__((always_inline)) {
+                    constexpr int A = Ai;
+                    const double us = ln.rec[o * kRec3v + A];
+                    const double F = fma(val[o], us, p * fma(isE, us, cm[A]));
+                    double(&r)[P] = A == 0 ? rx : (A == 1 ? ry : rz);
 #pragma unroll
-            for (int fi = 0; fi < FCH; ++fi) {
-                double e, o;
-                trace3<P, A>(K, f0 + fi, e, o);
-                if (live) lds[slot(fi, lc)] = e + o;
-                Tm[fi] = e - o;
-            }
-            __syncthreads();
-            // - face: left state = the + trace of the cell below
-#pragma unroll
-            for (int fi = 0; fi < FCH; ++fi) {
-                double tl;
-                if (in_m) {
-                    tl = lds[slot(fi, lc - stride)];
-                } else if (edge_m) { // slab edge inside the leaf: the layer below
-                    double e, o;
-                    trace3<P, A>(nb, f0 + fi, e, o);
-                    tl = e + o;
-                } else {
-                    tl = gt_m[long(f0 + fi) * layer];
-                }
-                Fm[fi] = rusanov_5<A>(tl, Tm[fi], addr0, g.gamma, isM, isE);
-                DG_PIN(Fm[fi]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int fi = 0; fi < FCH; ++fi)
-                if (live) lds[slot(fi, lc)] = Fm[fi];
-            __syncthreads();
-            // + face: computed by the cell above unless it is outside the slab
-            if (in_p) {
-#pragma unroll
-                for (int fi = 0; fi < FCH; ++fi) Fp[fi] = lds[slot(fi, lc + stride)];
-            } else {
-#pragma unroll
-                for (int fi = 0; fi < FCH; ++fi) {
-                    double e, o, tr;
-                    if (edge_p) { // slab edge inside the leaf: the layer above
-                        trace3<P, A>(nb, f0 + fi, e, o);
-                        tr = e - o;
-                    } else {
-                        tr = gt_p[long(f0 + fi) * layer];
+                    for (int i = 0; i < P; ++i) {
+                        // x: modes i + 1 through their derivative; y, z: modes i < P
+                        const double c = kRule<P>.w[qx] * (A == 0 ? kRule<P>.der[qx][i + 1] : kRule<P>.val[qx][i]);
+                        if (c != 0.0) r[i] = qx == 0 ? c * F : fma(c, F, r[i]);
+                        else if (qx == 0) r[i] = 0.0;
                     }
-                    trace3<P, A>(K, f0 + fi, e, o);
-                    Fp[fi] = rusanov_5<A>(e + o, tr, addr0, g.gamma, isM, isE);
-                    DG_PIN(Fp[fi]);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+                });
+                if constexpr (qx == Q - 1) // the row's fluxes onto the modes
+#pragma unroll
+                    for (int m = 0; m < NB; ++m) {
+                        const int i = kTab<3, P>.e[m][0], j = kTab<3, P>.e[m][1], k = kTab<3, P>.e[m][2];
+                        const double vz = kRule<P>.w[qz] * kRule<P>.val[qz][k], dz = kRule<P>.w[qz] * kRule<P>.der[qz][k];
+                        const double vy = kRule<P>.w[qy] * kRule<P>.val[qy][j], dy = kRule<P>.w[qy] * kRule<P>.der[qy][j];
+                        if (i > 0 && vy * vz != 0.0) R[m] = fma(vy * vz, rx[i - 1], R[m]);
+                        if (j > 0 && dy * vz != 0.0) R[m] = fma(dy * vz, ry[i], R[m]);
+                        if (k > 0 && vy * dz != 0.0) R[m] = fma(vy * dz, rz[i], R[m]);
+                        DG_PIN(R[m]);
+                    }
             }
-            // lift: R_m += s_a w phi_m(+1)/M_m ((-1)^{m_A} Phi_- - Phi_+)
-#pragma unroll
-            for (int fi = 0; fi < FCH; ++fi) {
-                const double dm = sc * Fm[fi], dp = sc * Fp[fi];
-                const double even = dm - dp, odd = -(dm + dp);
-#pragma unroll
-                for (int m = 0; m < NB; ++m) {
-                    const double c = kTab<3, P>.lift_f[A][f0 + fi][m];
-                    if (c != 0.0) R[m] = fma(c, (kTab<3, P>.e[m][A] % 2 == 0) ? even : odd, R[m]);
-                }
-            }
-#pragma unroll
-            for (int m = 0; m < NB; ++m) DG_PIN(R[m]);
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        static_for<0, NF / FCH>(chunk);
+        });
+        wave_lds_sync();
+        __builtin_amdgcn_sched_barrier(0);
     });
+}
 
-    // ---- fused RK stage (FP64), as the thread-per-cell kernel rounds it
-    double dt;
-    if (g.rate_in) {
-        dt = g.cfl / __longlong_as_double((long long)*g.rate_in);
-        if (blockIdx.x == 0 && threadIdx.x == 0) *g.dt_out = dt;
+// Flux of one face in its face modes, this lane's variable: to the own trace,
+// nbr(f) mode f of the neighbour's, side +1 / -1 the side of the own cell the
+// face is on.
+template <int P, int A, class Nbr>
+__device__ __forceinline__ void face_flux_3v(const double *to, Nbr &&nbr, double side, double gamma, const Lanes3 &ln,
+                                             double *Phi)
+{
+    constexpr int NF = Tab<3, P>::NF, Q = P + 1, NBF = face_modes<3, P>();
+    struct {
+    } none;
+    double ro[Q], rn[Q], acc[Q];
+#pragma unroll
+    for (int f = 0; f < NBF; ++f) Phi[f] = 0.0;
+    static_for<0, (NF + 4) / 5>([&](auto gv) __attribute__((always_inline)) {
+        static_for<0, 5>([&](auto ov) __attribute__((always_inline)) {
+            constexpr int o = ov, f = 5 * decltype(gv)::value + o;
+            if constexpr (f < NF) {
+                constexpr int t0 = f % Q, t1 = f / Q;
+                if constexpr (t0 == 0)
+#pragma unroll
+                    for (int j = 0; j < Q; ++j) {
+                        ro[j] = to[mode2(j, 0)];
+                        rn[j] = nbr(mode2(j, 0));
+#pragma unroll
+                        for (int k = 1; j + k < Q; ++k) {
+                            const double c = kRule<P>.val[t1][k];
+                            if (c != 0.0) {
+                                ro[j] = fma(c, to[mode2(j, k)], ro[j]);
+                                rn[j] = fma(c, nbr(mode2(j, k)), rn[j]);
+                            }
+                        }
+                    }
+                double uo = ro[0], un = rn[0];
+#pragma unroll
+                for (int j = 1; j < Q; ++j) {
+                    const double c = kRule<P>.val[t0][j];
+                    if (c != 0.0) {
+                        uo = fma(c, ro[j], uo);
+                        un = fma(c, rn[j], un);
+                    }
+                }
+                ln.put(o, 0, uo);
+                ln.put(o, 1, un);
+            }
+        });
+        wave_lds_sync();
+        {
+            double Uo[5], Un[5], F[5];
+#pragma unroll
+            for (int b = 0; b < 5; ++b) {
+                Uo[b] = ln.own[b];
+                Un[b] = ln.own[5 + b];
+            }
+            side_flux<3, A, EQ_EULER>(none, Uo, Un, side, gamma, F);
+#pragma unroll
+            for (int b = 0; b < 5; ++b) ln.own[b] = F[b];
+        }
+        wave_lds_sync();
+        static_for<0, 5>([&](auto ov) __attribute__((always_inline)) {
+            constexpr int o = ov, f = 5 * decltype(gv)::value + o;
+            if constexpr (f < NF) {
+                constexpr int t0 = f % Q, t1 = f / Q;
+                const double F = ln.get(o);
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    const double c = kRule<P>.w[t0] * kRule<P>.val[t0][j];
+                    if (c != 0.0) acc[j] = t0 == 0 ? c * F : fma(c, F, acc[j]);
+                    else if (t0 == 0) acc[j] = 0.0;
+                }
+                if constexpr (t0 == Q - 1)
+#pragma unroll
+                    for (int j = 0; j < Q; ++j)
+#pragma unroll
+                        for (int k = 0; j + k < Q; ++k) {
+                            const double c = kRule<P>.w[t1] * kRule<P>.val[t1][k];
+                            if (c != 0.0) Phi[mode2(j, k)] = fma(c, acc[j], Phi[mode2(j, k)]);
+                        }
+            }
+        });
+        wave_lds_sync();
+        __builtin_amdgcn_sched_barrier(0);
+    });
+}
+
+// R_m -= side^(m_A + 1) (2/h_A) Phi_f(m), this lane's variable (before M^-1)
+template <int P, int A>
+__device__ __forceinline__ void lift_3v(const double *Phi, double side, double sc, double *R)
+{
+    const double even = -side * sc;
+#pragma unroll
+    for (int m = 0; m < Tab<3, P>::NB; ++m)
+        R[m] = fma(kTab<3, P>.e[m][A] % 2 == 0 ? even : -sc, Phi[face_mode<3, P>(m, A)], R[m]);
+#pragma unroll
+    for (int m = 0; m < Tab<3, P>::NB; ++m) DG_PIN(R[m]);
+}
+
+// This lane's variable of the polynomial across block face (a, side) at
+// tangential index t: the guard cell, the neighbour's cell, its split or
+// combine, or at an outflow boundary the mirror image of the own cell (index
+// own in the leaf).
+template <int P, int GM>
+__device__ __forceinline__ void far_3v(const StageArgs &g, int leaf, int v, int a, int side, int t, int own, double *kf)
+{
+    constexpr int NV = 5, NB = Tab<3, P>::NB;
+    const int N = g.N, layer = N * N, ncell = layer * N;
+    const long sv = long(NB) * ncell;
+    if constexpr (GM == GUARD_BUFFER) {
+        const double *gk = g.guard + ((long(leaf) * 6 + 2 * a + (side > 0)) * NV + v) * NB * layer + t;
+#pragma unroll
+        for (int m = 0; m < NB; ++m) kf[m] = gk[long(m) * layer];
     } else {
-        dt = g.dt[g.leaf_member ? g.leaf_member[leaf] : 0];
-    }
-    if (g.rate_clear && blockIdx.x == 0 && threadIdx.x == 0) *g.rate_clear = 0ULL;
-    const double a = g.rk_a, b = g.rk_b;
+        const FaceLink L = g.links[leaf * 6 + 2 * a + (side > 0)];
+        if (L.type == dgamr::LINK_COARSE || L.type == dgamr::LINK_FINE) {
+            hanging_var<3, P, NV>(g, v, a, side, t, L, kf);
+        } else {
+            const bool mirror = L.type == dgamr::LINK_BOUNDARY;
+            const double *nk = g.us + (mirror ? long(leaf) : long(L.nbr[0])) * NV * sv + v * sv +
+                               (mirror ? own : same_cell(a, side, t, N, 3));
 #pragma unroll
-    for (int m = 0; m < NB; ++m) K[m] = b * (K[m] + dt * R[m]);
-    if (a != 0.0) { // uniform: stages 2 and 3 add the RK base state
-#pragma unroll
-        for (int m = 0; m < NB; ++m) K[m] = fma(a, g.un[idx0 + long(m) * ncell], K[m]);
+            for (int m = 0; m < NB; ++m) {
+                const int e = kTab<3, P>.e[m][0] * (a == 0) + kTab<3, P>.e[m][1] * (a == 1) + kTab<3, P>.e[m][2] * (a == 2);
+                kf[m] = nk[long(m) * ncell];
+                if (mirror && (e & 1)) kf[m] = -kf[m];
+            }
+        }
     }
-    if (live) {
-#pragma unroll
-        for (int m = 0; m < NB; ++m) g.out64[idx0 + long(m) * ncell] = K[m];
+}
+
+// What bounds it: the latencies of one layer's chain (two LDS round trips per
+// group of five points, the far traces and the RK base state) with three
+// waves per SIMD that the barriers keep in the same phase; at degree 3 also
+// registers (spills at 168).  8^3-cell blocks, average stage with everything
+// that goes before it: degree 2, 16^3 roots 2.52 ms (one thread per cell, one
+// wave per SIMD) -> 1.84 ms; degree 3, 8^3 roots 1.43 ms (every lane computing
+// every point's flux, faces in chunks with 12 barriers per axis, guard traces
+// written by a fill before) -> 1.02 ms.  One item of six waves per workgroup
+// took 2.60 ms at degree 2: 1.5 waves per SIMD.
+//
+// One (leaf, slab of `rows` layers) takes waves_item waves, 64 lanes per 12 of
+// the layer's N^2 cells and N + faces; a workgroup holds `group` of them, so
+// that its waves spread evenly over a compute unit's four SIMDs (a second
+// workgroup of six waves was not placed beside the first).  lds_item: doubles
+// of LDS per item.
+template <int P, int GM, int OM>
+__global__ __launch_bounds__(kThreads3v, waves_3v<P>()) void k_stage3v(StageArgs g, int rows, int waves_item, int group,
+                                                                          int lds_item)
+{
+    constexpr int NV = 5, NB = Tab<3, P>::NB, NBF = face_modes<3, P>(), PITCH = (NV * NBF) | 1;
+    // the RK base state loaded ahead of its use, where the registers allow (the
+    // next layer is to degree 2)
+    constexpr bool PREFETCH = P <= 1;
+    extern __shared__ double lds_all[];
+    const int N = g.N, layer = N * N, ncell = layer * N;
+    const int slabs = N / rows, items = g.nleaves * slabs;
+    const int wgwave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), sub = wgwave / waves_item;
+    const int item = xcd_leaf(blockIdx.x, gridDim.x) * group + sub;
+    const bool real = item < items; // the last workgroup may be partly empty: it repeats the last item
+    const int it0 = real ? item : items - 1;
+    const int li = it0 / slabs, k0 = (it0 % slabs) * rows;
+    const int leaf = g.work ? g.work[li] : li; // listed leaves of a pool, or all
+    const int lane = threadIdx.x & 63, wave = wgwave - sub * waves_item;
+    double *const lds = lds_all + sub * lds_item;
+    const int lv = lane < 5 * kCells3v ? lane : lane - 5; // lanes 60..63 repeat lanes 55..58
+    const int cw = lv / 5, v = lv - 5 * cw;
+    const int slot = wave * kCells3v + cw, nslots = waves_item * kCells3v;
+    // slots: the layer's cells, then the + faces of the last cells of its
+    // rows (x) or columns (y); the rest store nothing
+    const bool is_cell = slot < layer, live = real && lane < 5 * kCells3v && is_cell;
+    const bool active = lane < 5 * kCells3v && slot < layer + N;
+    const int c = is_cell ? slot : layer - 1; // spare slots repeat the last cell
+    const int j = div_n(c, g.inv_n), i = c - j * N;
+    const int pf = is_cell ? 0 : (slot - layer < N ? slot - layer : N - 1);
+    const double side = is_cell ? -1.0 : 1.0;
+    double *const recs = lds + wave * 5 * kCells3v * kRec3v;
+    const Lanes3 ln{recs + 5 * cw * kRec3v, recs + lv * kRec3v, v};
+    double *const T = lds + waves_item * 5 * kCells3v * kRec3v; // layer + 4 N slots of PITCH
+    double *const Tv = T + v * NBF;
+    const double isE = v == 4 ? 1.0 : 0.0;
+    const double isM[3] = {v == 1 ? 1.0 : 0.0, v == 2 ? 1.0 : 0.0, v == 3 ? 1.0 : 0.0};
+    const double sc[3] = {g.geo[leaf].scale[0], g.geo[leaf].scale[1], g.geo[leaf].scale[2]};
+    const double gm1 = g.gamma - 1.0;
+    const long sv = long(NB) * ncell;
+    // mode m's planes of this leaf in array X at a workgroup-uniform address;
+    // the lanes add one 32-bit offset
+    const long lbase = long(leaf) * NV * sv;
+    const unsigned uc = unsigned(v) * unsigned(sv) + unsigned(c);
+    auto plane = [&](auto *X, int m) __attribute__((always_inline)) { return X + (lbase + long(m) * ncell); };
+
+    double dt = 0.0;
+    if constexpr (OM == OUT_RK) {
+        if (g.rate_in) {
+            dt = g.cfl / __longlong_as_double((long long)*g.rate_in);
+            if (blockIdx.x == 0 && threadIdx.x == 0) *g.dt_out = dt;
+        } else {
+            dt = g.dt[g.leaf_member ? g.leaf_member[leaf] : 0];
+        }
+        if (g.rate_clear && blockIdx.x == 0 && threadIdx.x == 0) *g.rate_clear = 0ULL;
     }
-    if (g.rate_out) {
-        // CFL rate of the new state from its cell mean, folded over the slab
-        double U[5];
-        cell_state5(K[0], addr0, U);
-        const double rinv = 1.0 / U[0];
-        const double cs = sqrt(g.gamma * pressure_r<3>(U, gm1, rinv) * rinv);
-        double rate = 0.0;
+    // layer k of this lane's column; outside the leaf the polynomial across
+    // the z face
+    auto load_layer = [&](int k, double *X) __attribute__((always_inline)) {
+        if (k >= 0 && k < N) { // uniform
 #pragma unroll
-        for (int a2 = 0; a2 < 3; ++a2) rate += (fabs(U[1 + a2] * rinv) + cs) / g.geo[leaf].h[a2];
-        // every lane holds its cell's rate (unused lanes repeat a cell of the slab)
-        block_max_to(rate, lds, g.rate_out);
+            for (int m = 0; m < NB; ++m) X[m] = plane(g.us, m)[uc + unsigned(k * layer)];
+        } else {
+            far_3v<P, GM>(g, leaf, v, 2, k < 0 ? -1 : 1, c, c + (k < 0 ? 0 : N - 1) * layer, X);
+        }
+    };
+    double K[NB], Kn[NB], R[NB]; // current and next layer; R starts with the face below
+#pragma unroll
+    for (int m = 0; m < NB; ++m) R[m] = 0.0;
+    double rate = 0.0;
+    // per iteration: load the next layer, finish the current one (from
+    // it = 0), take the flux between them (from it = -1)
+#pragma unroll 1
+    for (int it = -2; it < rows; ++it) {
+        const int k = k0 + it;
+        if (P <= 2 || it < 0) load_layer(k + 1, Kn);
+        double Un[NB];
+        if (it >= 0) {
+            // traces across the leaf's x and y faces, spread over the waves (the
+            // first one is hidden from the compiler, which would otherwise hoist
+            // every address out of the layer loop into registers)
+            int s0 = cw * waves_item + wave;
+            asm volatile("" : "+v"(s0));
+            for (int s = s0; s < 4 * N; s += nslots) {
+                const int a = s < 2 * N ? 0 : 1, b0 = s - 2 * N * a, sd = b0 < N ? -1 : 1, b = b0 < N ? b0 : b0 - N;
+                const int n = sd < 0 ? 0 : N - 1;
+                double kf[NB], tr[NBF];
+                far_3v<P, GM>(g, leaf, v, a, sd, b + N * k, (a == 0 ? n + N * b : b + N * n) + k * layer, kf);
+                if (a == 0) face_trace<3, P, 0>(kf, double(-sd), tr);
+                else face_trace<3, P, 1>(kf, double(-sd), tr);
+                if (lane < 5 * kCells3v)
+#pragma unroll
+                    for (int f = 0; f < NBF; ++f) Tv[(layer + s) * PITCH + f] = tr[f];
+            }
+            if constexpr (P > 0) volume_3v<P>(K, R, ln, sc, gm1, isE, isM);
+            static_for<0, 2>([&](auto Ai) __attribute__((always_inline)) {
+                constexpr int A = Ai;
+                const int ia = A == 0 ? i : j, stride = A == 0 ? 1 : N, jb = A == 0 ? j : i;
+                double to[NBF], Phi[NBF];
+                face_trace<3, P, A>(K, 1.0, to);
+                if (is_cell && lane < 5 * kCells3v)
+#pragma unroll
+                    for (int f = 0; f < NBF; ++f) Tv[c * PITCH + f] = to[f];
+                __syncthreads();
+                // the - faces of the cells, and in the spare slots the + faces
+                // of the last cells; the flux modes replace T+
+                const int own = A == 0 ? (N - 1) + N * pf : pf + N * (N - 1);
+                const int ext = layer + 2 * N * A + (is_cell ? jb : N + pf);
+                const double *const nb = Tv + (is_cell && ia > 0 ? c - stride : ext) * PITCH;
+                if (is_cell) face_trace<3, P, A>(K, -1.0, to);
+                else
+#pragma unroll
+                    for (int f = 0; f < NBF; ++f) to[f] = Tv[own * PITCH + f];
+                face_flux_3v<P, A>(to, [&](int f) __attribute__((always_inline)) { return nb[f]; }, side, g.gamma, ln, Phi);
+                double *const dst = Tv + (is_cell ? c - stride : own) * PITCH;
+                if (active && (!is_cell || ia > 0))
+#pragma unroll
+                    for (int f = 0; f < NBF; ++f) dst[f] = Phi[f];
+                lift_3v<P, A>(Phi, -1.0, sc[A], R); // (a spare slot's R is not used)
+                __syncthreads();
+#pragma unroll
+                for (int f = 0; f < NBF; ++f) Phi[f] = Tv[c * PITCH + f];
+                lift_3v<P, A>(Phi, 1.0, sc[A], R);
+            });
+            if constexpr (P > 2) load_layer(k + 1, Kn);
+            if constexpr (OM == OUT_RK)
+                if (PREFETCH && g.rk_a != 0.0) // uniform: stages 2 and 3 add the RK base state
+#pragma unroll
+                    for (int m = 0; m < NB; ++m) Un[m] = plane(g.un, m)[uc + unsigned(k * layer)];
+        }
+        // the face above
+        double Pt[NBF];
+        if (it >= -1) {
+            double to[NBF], tn[NBF];
+            face_trace<3, P, 2>(K, 1.0, to);
+            face_trace<3, P, 2>(Kn, -1.0, tn);
+            face_flux_3v<P, 2>(to, [&](int f) __attribute__((always_inline)) { return tn[f]; }, 1.0, g.gamma, ln, Pt);
+        }
+        if (it >= 0) {
+            lift_3v<P, 2>(Pt, 1.0, sc[2], R);
+            const unsigned idx = uc + unsigned(k * layer);
+            if constexpr (OM == OUT_RES64) {
+                if (live)
+#pragma unroll
+                    for (int m = 0; m < NB; ++m) plane(g.out64, m)[idx] = R[m] * kTab<3, P>.inv_mass[m];
+            } else {
+                const double a = g.rk_a, b = g.rk_b;
+#pragma unroll
+                for (int m = 0; m < NB; ++m) K[m] = b * fma(dt * kTab<3, P>.inv_mass[m], R[m], K[m]);
+                if (a != 0.0) {
+#pragma unroll
+                    for (int m = 0; m < NB; ++m) K[m] = fma(a, PREFETCH ? Un[m] : plane(g.un, m)[idx], K[m]);
+                }
+                if (live)
+#pragma unroll
+                    for (int m = 0; m < NB; ++m) plane(g.out64, m)[idx] = K[m];
+                if (g.rate_out) {
+                    // CFL rate of the new state from its cell mean
+                    ln.put(0, 0, K[0]);
+                    wave_lds_sync();
+                    double U[5];
+#pragma unroll
+                    for (int b2 = 0; b2 < 5; ++b2) U[b2] = ln.rec[b2];
+                    wave_lds_sync();
+                    const double rinv = 1.0 / U[0];
+                    const double cs = sqrt(g.gamma * pressure_r<3>(U, gm1, rinv) * rinv);
+                    double r = 0.0;
+#pragma unroll
+                    for (int a2 = 0; a2 < 3; ++a2) r += (fabs(U[1 + a2] * rinv) + cs) / g.geo[leaf].h[a2];
+                    rate = nan_max(rate, r);
+                }
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < NB; ++m) {
+            K[m] = Kn[m];
+            R[m] = 0.0;
+        }
+        if (it >= -1) lift_3v<P, 2>(Pt, -1.0, sc[2], R);
     }
+    // every lane holds a rate of its column (spare slots the last cell's)
+    if constexpr (OM == OUT_RK)
+        if (g.rate_out) block_max_to(rate, lds_all, g.rate_out);
 }
 
 } // namespace dgk

@@ -7,7 +7,9 @@
 //    take 100 (degree 2) or 200 of its 256 doubles.  At degree 3 the
 //    axis-by-axis form spills 2.7 KB per lane and 13 000 scalars, and one of
 //    its builds returned wrong momenta in the residual of a conservative
-//    hanging forest (the same source, compiled otherwise, passed).
+//    hanging forest (the same source, compiled otherwise, passed).  Steps
+//    run one lane per (cell, variable) there (kernels_3d.hpp) unless they have
+//    the limiter or mortar faces.
 #pragma once
 
 #include "kernels.hpp"

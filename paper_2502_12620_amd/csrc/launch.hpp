@@ -22,34 +22,24 @@ struct StageShape {
     int mfma = 0; // FP32 residual: 1 = the volume integral on the matrix cores where built
 };
 
-// 3-D lane-per-(cell, variable) kernel: 12 cells per wave, at most 12 waves
-// per workgroup; a slab is whole layers, at least two of them (so that only
-// z faces can be slab edges and a cell has at most one) unless it is the
-// whole leaf
+// 3-D lane-per-(cell, variable) kernel: 12 cell slots per wave, one layer of
+// a block and its N + faces at a time, 6 waves at N = 8; a workgroup holds
+// as many blocks as make a multiple of four waves (two at N = 8).  A slab
+// height asked for: whole layers, at least two unless it is the whole leaf,
+// at most 144 cells.
 constexpr int kCells3v = 12;
 constexpr int kThreads3v = 768;
 inline bool rows_ok_3v(int N, int rows)
 {
-    return rows >= 1 && N % rows == 0 && (rows >= 2 || rows == N) && rows * N * N <= kCells3v * (kThreads3v / 64);
+    return rows >= 1 && N % rows == 0 && (rows >= 2 || rows == N) && rows * N * N <= 144;
 }
 
-// largest slab height the 3-D lane kernel takes for block size N (0: none)
-inline int rows_3v(int N)
+// Whether a 3-D stage runs the lane kernel: it is asked for (variant 0) and
+// takes the case (FP64 Euler without the limiter and without mortar faces).
+inline bool lanes_3d(const StageShape &sh, bool limiter, bool fp32, bool conservative, bool advection, int N)
 {
-    for (int r = N; r >= 1; --r)
-        if (rows_ok_3v(N, r)) return r;
-    return 0;
-}
-
-// Whether the fused stage of a 3-D Euler forest runs the lane kernel, which
-// reads the far side of block faces as traces written by the fill kernel
-// before the stage (the thread-per-cell kernel computes it inline): the
-// lane kernel is asked for (variant 0) and takes the case.
-inline bool stage_reads_traces(int dim, const StageShape &sh, bool limiter, bool fp32, bool conservative,
-                               bool advection, int N)
-{
-    return dim == 3 && !advection && !fp32 && !limiter && !conservative && sh.variant == 0 &&
-           (sh.rows == 0 ? rows_3v(N) > 0 : rows_ok_3v(N, sh.rows));
+    return !advection && !fp32 && !limiter && !conservative && sh.variant == 0 &&
+           (sh.rows == 0 || rows_ok_3v(N, sh.rows));
 }
 
 // residual / fused stage.  fp32: residual arithmetic in FP32 (out_mode

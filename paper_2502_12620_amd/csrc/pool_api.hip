@@ -137,19 +137,8 @@ int pool_stage(dgamr_pool *p, int stage, const double *us, const double *un, dou
     a.conservative = p->cls.hanging == DGAMR_HANG_CONSERVATIVE;
     const bool lim = p->cls.limiter == DGAMR_LIMITER_POSITIVITY;
     const bool fp32 = p->cls.precision == DGAMR_FP32;
-    int gm = dgk::GUARD_INLINE;
-    // the 3-D lane kernel reads guard traces of the listed leaves' faces
-    if (dgk::stage_reads_traces(p->dim, sh, lim, fp32, a.conservative != 0, false, p->N)) {
-        gm = dgk::GUARD_TRACE;
-        a.guard = w.guard;
-        dgk::FillArgs fa{us, w.guard, p->d_links, nullptr, p->d_work, p->nwork * 2 * p->dim, p->N, 1, 0};
-        CHECK(dispatch(p->dim, p->degree, [&](auto D, auto P) -> int {
-            HIP_TRY((dgk::launch_fill<D, P>(fa, p->nfc, s)));
-            return DGAMR_OK;
-        }));
-    }
     return dispatch(p->dim, p->degree, [&](auto D, auto P) -> int {
-        HIP_TRY((dgk::launch_stage<D, P>(a, gm, dgk::OUT_RK, lim, fp32, sh, s)));
+        HIP_TRY((dgk::launch_stage<D, P>(a, dgk::GUARD_INLINE, dgk::OUT_RK, lim, fp32, sh, s)));
         return DGAMR_OK;
     });
 }
@@ -216,8 +205,8 @@ int dgamr_pool_create(const dgamr_forest_desc *cls, int64_t capacity_leaves, int
         p->ncell = cls->dim == 2 ? p->N * p->N : p->N * p->N * p->N;
         p->nfc = cls->dim == 2 ? p->N : p->N * p->N;
         p->cap = capacity_leaves;
-        // default stage kernel as for a single forest of the class: one lane
-        // per (cell, variable) in 3-D at degree 3, one thread per cell else
+        // default stage kernel: one lane per (cell, variable) in 3-D at degree
+        // 3, one thread per cell else (until the shape is set or autotuned)
         if (p->dim == 3 && p->degree >= 3 && lanes_class(p)) p->shape.variant = 0;
         p->maxm = max_members;
         p->used.assign(size_t(capacity_leaves), 0);
