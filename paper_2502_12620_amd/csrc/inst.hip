@@ -2,13 +2,14 @@
 // launchers; compiled once per pair with -DDG_D=<dim> -DDG_P=<degree> and
 // -DDG_PART=<part>, the heavy kernels split over parts so that the units
 // compile in parallel:
-//   part 0  the dispatcher launch_stage, the lane-per-(cell, variable)
+//   part 0  the dispatcher launch_stage, the 2-D lane-per-(cell, variable)
 //           kernels, scalar convection, fill, limiter, projection, inheritance
 //   part 1  the thread-per-cell Euler stage kernels in FP64
 //   part 2  the thread-per-cell Euler stage kernels with FP32 arithmetic
 //   part 3  the diffusion stage
 //   part 4  the thread-per-cell Euler stage kernels with FP32 arithmetic and
 //           the volume integral on the matrix cores (degree >= 2)
+//   part 5  the 3-D lane-per-(cell, variable) stage kernels
 #include "kernels.hpp"
 #include "kernels_2d.hpp"
 #include "kernels_3d.hpp"
@@ -42,7 +43,9 @@ hipError_t launch_stage_2v(const StageArgs &a, int gm, int om, hipStream_t s, in
         rows = rows_req;
     } else {
         while (rows * a.N * 4 > 512) rows /= 2;
-        while (rows % 2 == 0 && rows > 1 && long(a.nleaves) * (a.N / rows) < 256) rows /= 2;
+        // thinner slabs until every compute unit has one, of at least a whole
+        // wave (16 leaves of 8^2 cells, degree 1: 2 rows 6.7 us, 1 row 7.6)
+        while (rows % 2 == 0 && rows * a.N * 4 >= 128 && long(a.nleaves) * (a.N / rows) < 256) rows /= 2;
     }
     const int slabs = a.N / rows;
     const size_t lds = sizeof(double) * (P + 1) * rows * a.N * 4;
@@ -119,7 +122,25 @@ hipError_t launch_stage_cell(const StageArgs &args, int gm, int om, bool lim, co
     int rows = sh.rows;
     if (rows == 0) {
         rows = a.N;
-        while (rows % 2 == 0 && rows * layer > stage_default_cells<D, P, T>()) rows /= 2;
+        if constexpr (by_axis<D, P, T>()) {
+            // the slab that fills its waves best; among equals the tallest of
+            // at most stage_default_cells cells (12^2-cell blocks, 100^2 roots,
+            // degree 2: 4 rows, 48 of 64 lanes, 213 us; 6 rows, 72 of 128, 271;
+            // 12 rows, 144 of 192, 261)
+            double best = 0.0;
+            for (int r = a.N; r >= 1; --r) {
+                if (!rows_ok<D, P, T>(a.N, r)) continue;
+                const int cells = r * layer;
+                double fill = cells / (64.0 * ((cells + 63) / 64));
+                if (cells > stage_default_cells<D, P, T>()) fill -= 1e-3;
+                if (fill > best) {
+                    best = fill;
+                    rows = r;
+                }
+            }
+        } else {
+            while (rows % 2 == 0 && rows * layer > stage_default_cells<D, P, T>()) rows /= 2;
+        }
     }
     if (!rows_ok<D, P, T>(a.N, rows)) return hipErrorInvalidValue;
     const int nslab = rows * layer;
@@ -196,7 +217,7 @@ hipError_t launch_stage_cell(const StageArgs &args, int gm, int om, bool lim, co
                                lds, s, a, rows);
             return hipGetLastError();
         }
-    } else if constexpr (D == 3) { // the 2-D FP64 residual runs one lane per (cell, variable)
+    } else {
         if (gm == GUARD_BUFFER && om == OUT_RES64) {
             hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RES64, false, T>), grid_all, block, lds, s, a, rows);
             return hipGetLastError();
@@ -206,7 +227,10 @@ hipError_t launch_stage_cell(const StageArgs &args, int gm, int om, bool lim, co
 }
 
 #if DG_PART == 0
-// defined here, instantiated in parts 1 and 2
+// defined here, instantiated in parts 1, 2 and 5
+#if DG_D == 3
+extern template hipError_t launch_stage_3v<DG_P>(const StageArgs &, int, int, hipStream_t, int);
+#endif
 extern template hipError_t launch_stage_cell<DG_D, DG_P, double, EQ_EULER>(const StageArgs &, int, int, bool,
                                                                           const StageShape &, hipStream_t);
 extern template hipError_t launch_stage_cell<DG_D, DG_P, float, EQ_EULER>(const StageArgs &, int, int, bool,
@@ -234,9 +258,13 @@ hipError_t launch_stage(const StageArgs &a, int gm, int om, bool lim, bool fp32,
         return launch_stage_cell<D, P, float>(a, gm, om, lim, sh, s);
     }
     if constexpr (D == 2) {
-        // one lane per (cell, variable) unless the caller asks for one
-        // thread per cell (variant 1) or needs the limiter
-        if (!lim && (sh.variant == 0 || om != OUT_RK)) return launch_stage_2v<P>(a, gm, om, s, sh.rows);
+        // one lane per (cell, variable) where asked for (variant 0: small
+        // forests), without the limiter.  The residual of large forests runs
+        // one thread per cell too (52 x 47 roots of 12^2 cells, 12 refined
+        // leaf rows, degree 3: 536 -> 205 us)
+        if (!lim && sh.variant == 0) return launch_stage_2v<P>(a, gm, om, s, sh.rows);
+        // (slab heights of the residual stay those of the lane kernel)
+        if (om != OUT_RK && sh.rows > 0 && (a.N % sh.rows != 0 || sh.rows * a.N * 4 > 512)) return hipErrorInvalidValue;
     } else {
         if (lanes_3d(sh, lim, false, a.conservative != 0, false, a.N)) return launch_stage_3v<P>(a, gm, om, s, sh.rows);
     }
@@ -368,6 +396,10 @@ template hipError_t launch_mapped_rate<DG_D, DG_P>(const MappedArgs &, int, int,
 template hipError_t launch_mapped_totals<DG_D, DG_P>(const MappedArgs &, int, int, int, double *, hipStream_t);
 template hipError_t launch_mapped_ic<DG_D, DG_P>(double *, const LeafGeo *, int, long, int, const IcParams &, double,
                                                  double, int, hipStream_t);
+#endif
+#elif DG_PART == 5
+#if DG_D == 3
+template hipError_t launch_stage_3v<DG_P>(const StageArgs &, int, int, hipStream_t, int);
 #endif
 #elif DG_PART == 1
 template hipError_t launch_stage_cell<DG_D, DG_P, double, EQ_EULER>(const StageArgs &, int, int, bool,

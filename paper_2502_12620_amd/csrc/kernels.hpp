@@ -749,21 +749,22 @@ __device__ __forceinline__ void volume_rows(const double (&K)[nvar<D, EQ>()][Tab
 // (3-D degree 2 in FP32 at 512 threads spills ~600 bytes per lane)
 template <int D, int P, typename T = double>
 constexpr int stage_threads() { return (D == 3 && P <= 1) ? 512 : 256; }
-// default slab (cells per workgroup) when the caller does not choose one:
-// the whole budget, except 3-D degree <= 1 and 2-D degree 1 and 2, where
-// 128-cell slabs let several workgroups share a compute unit and hide each
-// other's barriers (measured on 8^3 blocks at degree 1: 512-cell slabs
-// 671 us, 256: 582 us, 128: 564 us; 16^2 blocks at degree 2: 256-cell
-// slabs 184 us, 128: 171 us; 128^2 roots of 16^2 cells at degree 1:
-// 256-cell slabs 330 us, 128: 311 us, 64: 323 us; 16^3 roots of 8^3 cells
-// at degree 2 in FP64: 256-cell slabs 2.68 ms, 128: 2.53 ms, while in FP32
-// 2.18 against 2.21 ms; 64^2 roots of 16^2 cells at degree 3 in FP64: 256
-// cells 596 us, 128: 508 us, 64: 514 us, while in FP32 801 against 817 us)
+// default slab (cells per workgroup) when the caller does not choose one.
+// Axis by axis (FP64, 2-D and 3-D to degree 1): 128 cells, so that several
+// workgroups share a compute unit and hide each other's barriers, and one wave
+// at 2-D degree 3, which runs one wave per SIMD (40^2 roots of 16^2 cells:
+// degree 1 64 / 128 / 256 cells 32.7 / 30.7 / 32.3 us; degree 2 57.7 / 54.7 /
+// 60.8; degree 3 124.6 / 136.8 / 152.6; 3-D degree 1, 12^3 roots of 8^3 cells
+// 128 / 256 / 512 cells 153 / 150 / 183 us).  Point by point: 3-D degree 2 in
+// FP64 128 cells (256: 2.68 -> 2.53 ms on 16^3 roots), in FP32 the whole budget
+// (2.18 against 2.21 ms), as at degree 3, and 128 cells for the other FP32
+// kernels below.
 template <int D, int P, typename T = double>
 constexpr int stage_default_cells()
 {
+    if (D == 2 && P == 3 && sizeof(T) == 8) return 64;
     return ((D == 3 && P <= 1) || (D == 3 && P == 2 && sizeof(T) == 8) || (D == 2 && (P == 1 || P == 2)) ||
-            (D == 2 && P == 3 && sizeof(T) == 8))
+            (D == 2 && P == 0 && sizeof(T) == 8))
                ? 128
                : stage_threads<D, P, T>();
 }

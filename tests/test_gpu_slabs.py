@@ -37,3 +37,25 @@ def test_slab_shapes_against_the_oracle(dim, p, N, rows, mode):
     got = _host(ud)
     assert np.isfinite(got).all()
     assert rel_diff(got, u).max() <= TOL
+
+
+# The residual alone on the thread-per-cell kernel (the lane kernel takes small
+# forests): automatic slabs at block sizes that fill whole and partial waves,
+# one-row slabs and the whole leaf.
+@pytest.mark.parametrize("dim,p,N,rows", [(2, 0, 6, 0), (2, 1, 10, 1), (2, 1, 12, 0), (2, 2, 10, 0), (2, 2, 16, 16),
+                                          (2, 3, 4, 0), (2, 3, 16, 0), (2, 3, 12, 3), (3, 1, 6, 2)])
+def test_residual_alone_against_the_oracle(dim, p, N, rows):
+    from paper_2502_12620_amd import dgamr as G
+
+    w = _forest(dim, p, N, 3 if N <= 6 else 2, bc=W.OUTFLOW if rows else W.PERIODIC)
+    orc, gpu = make_pair(w, hanging=0)
+    gpu.set_tuning(G.TUNE_STAGE_VARIANT, 1)
+    gpu.set_tuning(G.TUNE_SLAB_ROWS, rows)
+    u = _physical_state(orc, w, seed=3 + p + N)
+    ud, gd, rd = _cuda(u), gpu.new_guard(), gpu.new_residual()
+    gpu.fill_guardcells(ud, gd)
+    gpu.dg_residual(ud, gd, rd)
+    assert rel_diff(_host(rd), orc.residual(u)).max() <= TOL
+    with pytest.raises(G.DgamrError):  # a slab height that is no divisor
+        gpu.set_tuning(G.TUNE_SLAB_ROWS, N - 1 if N > 2 else 3)
+        gpu.dg_residual(ud, gd, rd)
