@@ -461,9 +461,9 @@ __global__ __launch_bounds__(kThreads3v, waves_3v<P>()) void k_stage3v(StageArgs
         }
         if (it >= -1) lift_3v<P, 2>(Pt, -1.0, sc[2], R);
     }
-    // every lane holds a rate of its column (spare slots the last cell's)
+    // (a spare slot's state took a + face's flux for a - face's: no cell's rate)
     if constexpr (OM == OUT_RK)
-        if (g.rate_out) block_max_to(rate, lds_all, g.rate_out);
+        if (g.rate_out) block_max_to(is_cell ? rate : 0.0, lds_all, g.rate_out);
 }
 
 } // namespace dgk

@@ -129,3 +129,24 @@ def test_3d_thread_per_cell_conservative_mode_against_the_oracle(p, bc):
     for _ in range(3):
         orc.step(u, 0.1)
     assert rel_diff(got, u).max() <= TOL
+
+
+# The CFL rate folded into the stages, where the fastest cells are the last
+# ones of every layer: those that the lanes without a cell of their own repeat.
+@pytest.mark.parametrize("p,N", [(1, 4), (2, 2), (2, 4), (2, 6), (2, 8), (3, 4), (3, 6)])
+def test_rate_of_a_run_is_that_of_its_cells(p, N):
+    G = _G()
+    w = _forest(3, p, N, 2)
+    orc, gpu = make_pair(w)
+    u = _physical_state(orc, w, seed=5 * p + N)
+    last = np.arange(N) * N * N + N * N - 1
+    rho, mx = u[:, 0, 0, :][:, last], u[:, 1, 0, :][:, last]
+    u[:, 4, 0, last] += 0.5 * ((mx + 2.0 * rho) ** 2 - mx ** 2) / rho
+    u[:, 1, 0, last] += 2.0 * rho
+    gpu.set_tuning(G.TUNE_STAGE_VARIANT, 0)
+    ud, work, dt = _cuda(u), gpu.new_work(), torch.zeros(1, dtype=torch.float64, device="cuda")
+    gpu.run(ud, work, dt, 4, 0.05)
+    for _ in range(4):
+        dref = orc.step(u, 0.05)
+    assert rel_diff(_host(ud), u).max() <= TOL
+    assert abs(_host(dt)[0] - dref) <= 1e-12 * dref
