@@ -179,7 +179,7 @@ __device__ __forceinline__ void stage_item_points(const StageArgs &g, int rows, 
             T s = T(0);
 #pragma unroll
             for (int m = 0; m < NB; ++m) {
-                const double c = kTab<D, P>.phi_v[q][m];
+                const double c = kTake32<D, P, T> ? kPointTab32<D, P>.phi_v[q][m] : kTab<D, P>.phi_v[q][m];
                 if (use_entry<D, P>(c)) s = fma(T(c), K[v][m], s);
             }
             U[v] = s;
@@ -198,7 +198,7 @@ __device__ __forceinline__ void stage_item_points(const StageArgs &g, int rows, 
             for (int v = 0; v < NV; ++v) F[v] *= scale[A];
 #pragma unroll
             for (int m = 0; m < NB; ++m) {
-                const double c = kTab<D, P>.dproj[A][q][m];
+                const double c = kTake32<D, P, T> ? kPointTab32<D, P>.dproj[A][q][m] : kTab<D, P>.dproj[A][q][m];
                 // a mode of degree 0 along A has no derivative along A
                 if (kTab<D, P>.e[m][A] != 0 && use_entry<D, P>(c)) {
 #pragma unroll
@@ -382,7 +382,7 @@ __device__ __forceinline__ void stage_item_points(const StageArgs &g, int rows, 
                     const T even = dm - dp, odd = -(dm + dp);
 #pragma unroll
                     for (int m = 0; m < NB; ++m) {
-                        const double c = kTab<D, P>.lift_f[A][F][m];
+                        const double c = kTake32<D, P, T> ? kPointTab32<D, P>.lift_f[A][F][m] : kTab<D, P>.lift_f[A][F][m];
                         if (use_entry<D, P>(c)) R[v][m] = fma(T(c), (kTab<D, P>.e[m][A] % 2 == 0) ? even : odd, R[v][m]);
                     }
                 }
