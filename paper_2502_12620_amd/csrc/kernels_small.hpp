@@ -73,6 +73,42 @@ static __global__ __launch_bounds__(1024) void k_dt_final(const double *leaf_max
     if (threadIdx.x == 0) *dt = cfl / red[0];
 }
 
+// dt of a small forest in one launch (a launch's own latency bounds it, about
+// 3 us): one workgroup takes the CFL rate of every cell (k_rate's arithmetic; the maximum does not depend on the order)
+// and writes dt = cfl / max, with the maximum in leaf_max[0] for leaf_max ==
+// 0 .. n - 1 (k_rate_slot reads them all).
+template <int D>
+__global__ __launch_bounds__(1024) void k_rate_small(const double *u, const LeafGeo *geo, int N, int nb, int n,
+                                                     double gamma, double cfl, double *leaf_max, double *dt)
+{
+    constexpr int NV = D + 2;
+    __shared__ double red[16];
+    const int ncell = D == 2 ? N * N : N * N * N;
+    const long sv = long(nb) * ncell;
+    double mx = 0.0;
+    for (int i = threadIdx.x; i < n * ncell; i += blockDim.x) {
+        const int leaf = i / ncell, c = i - leaf * ncell;
+        const double *p = u + long(leaf) * NV * sv + c;
+        double U[NV];
+        for (int v = 0; v < NV; ++v) U[v] = p[v * sv];
+        double rinv = 1.0 / U[0];
+        double cs = sqrt(gamma * pressure<D>(U, gamma - 1.0) * rinv);
+        double rate = 0.0;
+        for (int a = 0; a < D; ++a) rate += (fabs(U[1 + a] * rinv) + cs) / geo[leaf].h[a];
+        mx = rate > mx ? rate : mx; // NaN never wins; caught by the state check
+    }
+    for (int off = 32; off >= 1; off >>= 1) {
+        const double o = __shfl_xor(mx, off);
+        mx = o > mx ? o : mx;
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    mx = red[0];
+    for (int w = 1; w < int(blockDim.x >> 6); ++w) mx = red[w] > mx ? red[w] : mx;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) leaf_max[i] = mx;
+    if (threadIdx.x == 0) *dt = cfl / mx;
+}
+
 // The max over leaves of the CFL rate, stored as the bit pattern of the
 // (non-negative) double in a rate slot of the fused-time-step scheme.
 static __global__ __launch_bounds__(1024) void k_rate_slot(const double *leaf_max, int n, unsigned long long *slot)
