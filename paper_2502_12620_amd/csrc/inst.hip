@@ -261,7 +261,7 @@ hipError_t launch_stage(const StageArgs &a, int gm, int om, bool lim, bool fp32,
         // one lane per (cell, variable) where asked for (variant 0: small
         // forests), without the limiter.  The residual of large forests runs
         // one thread per cell too (52 x 47 roots of 12^2 cells, 12 refined
-        // leaf rows, degree 3: 536 -> 205 us)
+        // leaf rows, degree 3: 536 -> 202 us)
         if (!lim && sh.variant == 0) return launch_stage_2v<P>(a, gm, om, s, sh.rows);
         // (slab heights of the residual stay those of the lane kernel)
         if (om != OUT_RK && sh.rows > 0 && (a.N % sh.rows != 0 || sh.rows * a.N * 4 > 512)) return hipErrorInvalidValue;

@@ -834,10 +834,10 @@ constexpr int stage_default_cells()
                : stage_threads<D, P, T>();
 }
 // waves per SIMD the register budget is cut for, chosen by measurement on
-// large forests: 2-D degree 1 in FP32 fits 128 registers (four waves);
-// 2-D degree 2 in FP64 spills 44 bytes per lane to run two waves per SIMD
-// instead of one (-20% time); 2-D degree 3 in FP32 runs two waves with 212
-// bytes of spills (-18%), while in FP64 (536 bytes) that is slower; 3-D
+// large forests: 2-D degree 1 in FP32 fits 128 registers (four waves), in FP64
+// 160 (three, without a bound); 2-D degree 2 in FP64 fits 255 with 12 bytes per
+// lane spilled (two waves; 2-D degree 3 at two waves spills 1 KB); 2-D degree 3
+// in FP32 runs two waves with 212 bytes of spills (-18%); 3-D
 // degree 1 in FP32 fits 164 registers (three waves; four: 335 -> 550 us on
 // 16^3 roots); 3-D degree 2 in FP32 runs two waves with 268 bytes of
 // spills (16^3 roots: 3.46 -> 2.17 ms), while three waves (more spills)

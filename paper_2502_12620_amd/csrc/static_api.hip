@@ -12,7 +12,7 @@ using namespace dgapi;
 
 namespace {
 
-// The work area: stage states U1 and U2, guard traces, leaf maxima and
+// The work area: stage states U1 and U2, guard cells, leaf maxima and
 // scalars, laid out as in the caller-owned work buffer of dgamr_step.  One
 // copy per GPU, held until the process ends.
 constexpr size_t kStaticWorkBytes = size_t(DGAMR_STATIC_WORK_BYTES);

@@ -76,7 +76,7 @@ class _Class:
 
 def slot_bytes(dim: int, degree: int, n_cell: int) -> int:
     """Bytes per leaf slot of a pool: the arena's state, the two stage
-    states and the guard traces of the work buffer, and the leaf maximum."""
+    states and the guard cells of the work buffer, and the leaf maximum."""
     nb = {2: [1, 3, 6, 10], 3: [1, 4, 10, 20]}[dim][degree]
     leaf = 8 * (dim + 2) * nb * n_cell ** dim
     guard = 8 * 2 * dim * (dim + 2) * nb * n_cell ** (dim - 1)
