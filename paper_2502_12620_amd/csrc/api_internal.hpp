@@ -78,10 +78,7 @@ struct dgamr_forest {
     int cap = 0;             // leaves the device tables can hold
     bool prof = false;       // bracket stage launches with events
     int stage_variant = -1;  // 2-D stage kernel: -1 auto, 0 lane per (cell, var), 1 thread per cell
-    // auto: lane per (cell, var) up to this many cells (28 672 cells, two-level
-    // degree 2: 14.4 against 18.0 us; 36 864 cells, degree 1 / 2 / 3: 14.1 / 26.3 /
-    // 40.9 against 11.7 / 16.8 / 21.6 us)
-    long var_split_max_cells = 32768;
+    long var_split_max_cells = -1; // 2-D auto: lane per (cell, var) up to this many cells, -1 = by rule
     int slab_rows = 0;       // layers of the last axis per stage workgroup, 0 = automatic
     int mfma = 0;            // FP32 residual: 1 = volume integral on the matrix cores where built
     std::vector<hipEvent_t> ev_free;

@@ -108,12 +108,15 @@ int stage_variant(const dgamr_forest *f)
     // 3-D: one lane per (cell, variable) from degree 2, where one thread's
     // state and residual leave one wave per SIMD; one thread per cell below
     if (f->topo.dim() == 3) return f->topo.desc().degree >= 2 ? 0 : 1;
+    const long cells = long(f->topo.n()) * ncell_of(f);
+    if (f->var_split_max_cells >= 0) return cells <= f->var_split_max_cells ? 0 : 1;
     // 2-D: one lane per (cell, variable) for small forests, where a launch is
     // one wave's life, and for blocks of at most 4^2 cells, where one thread per
     // cell leaves most of a wave idle (90^2 roots of 4^2 cells, degree 2: 42
-    // against 57 us)
-    if (f->topo.desc().n_cell <= 4) return 0;
-    return long(f->topo.n()) * ncell_of(f) <= f->var_split_max_cells ? 0 : 1;
+    // against 57 us).  The line: 28 672 cells, two-level degree 2: 14.4 against
+    // 18.0 us; 36 864 cells, degree 1 / 2 / 3: 14.1 / 26.3 / 40.9 against 11.7 /
+    // 16.8 / 21.6 us.
+    return f->topo.desc().n_cell <= 4 || cells <= 32768 ? 0 : 1;
 }
 
 dgk::StageShape stage_shape(const dgamr_forest *f)
