@@ -77,6 +77,7 @@ struct dgamr_forest {
     size_t plans_cap = 0;
     int cap = 0;             // leaves the device tables can hold
     bool prof = false;       // bracket stage launches with events
+    bool mortar = false;     // conservative hanging mode and some face has finer leaves
     int stage_variant = -1;  // 2-D stage kernel: -1 auto, 0 lane per (cell, var), 1 thread per cell
     long var_split_max_cells = -1; // 2-D auto: lane per (cell, var) up to this many cells, -1 = by rule
     int slab_rows = 0;       // layers of the last axis per stage workgroup, 0 = automatic

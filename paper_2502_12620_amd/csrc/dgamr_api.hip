@@ -2,6 +2,7 @@
 // refinement, and the launches of the HIP kernels.  See include/dgamr.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -78,6 +79,9 @@ int upload(dgamr_forest *f)
     std::vector<LeafGeo> geo = f->topo.geometry();
     HIP_TRY(hipMemcpy(f->d_geo, geo.data(), sizeof(LeafGeo) * n, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(f->d_links, f->topo.links().data(), sizeof(FaceLink) * size_t(n) * nf, hipMemcpyHostToDevice));
+    f->mortar = f->topo.desc().hanging == DGAMR_HANG_CONSERVATIVE &&
+                std::any_of(f->topo.links().begin(), f->topo.links().end(),
+                            [](const FaceLink &L) { return L.type == dgamr::LINK_FINE; });
     const auto &plans = f->topo.plans();
     if (plans.size() > f->plans_cap) {
         if (f->d_plans) HIP_TRY(hipFree(f->d_plans));
@@ -102,27 +106,43 @@ int launch_fill(dgamr_forest *f, const double *u, double *guard, hipStream_t s)
     });
 }
 
-int stage_variant(const dgamr_forest *f)
+int stage_variant(const dgamr_forest *f, int om)
 {
     if (f->stage_variant >= 0) return f->stage_variant;
+    const int N = f->topo.desc().n_cell, P = f->topo.desc().degree;
     // 3-D: one lane per (cell, variable) from degree 2, where one thread's
     // state and residual leave one wave per SIMD; one thread per cell below
-    if (f->topo.dim() == 3) return f->topo.desc().degree >= 2 ? 0 : 1;
+    if (f->topo.dim() == 3) return P >= 2 ? 0 : 1;
     const long cells = long(f->topo.n()) * ncell_of(f);
     if (f->var_split_max_cells >= 0) return cells <= f->var_split_max_cells ? 0 : 1;
     // 2-D: one lane per (cell, variable) for small forests, where a launch is
     // one wave's life, and for blocks of at most 4^2 cells, where one thread per
     // cell leaves most of a wave idle (90^2 roots of 4^2 cells, degree 2: 42
-    // against 57 us).  The line: 28 672 cells, two-level degree 2: 14.4 against
-    // 18.0 us; 36 864 cells, degree 1 / 2 / 3: 14.1 / 26.3 / 40.9 against 11.7 /
-    // 16.8 / 21.6 us.
-    return f->topo.desc().n_cell <= 4 || cells <= 32768 ? 0 : 1;
+    // against 57 us).
+    if (N <= 4) return 0;
+    // Mortar faces cost a thread per cell a long serial chain (both sides'
+    // traces, the flux and its lift for all variables), a lane a quarter of it.
+    // A step with one root in ten refined, lanes against thread per cell, 8^2 /
+    // 16^2 cells a block, at 40 000 cells: degree 2 68 / 93 against 145 / 105 us,
+    // degree 3 114 / 151 against 322 / 205; at 125 000: 125 / 168 against 129 / 180
+    // and 228 / 277 against 313 / 418; at 300 000: 237 / 339 against 213 / 220 and
+    // 454 / 573 against 563 / 533.  Earlier at degree 1 (10^2 cells, 80 000: 74
+    // against 67) and on 12^2 cells (degree 2, 80 000: 158 against 126), whose rows
+    // fill the lanes' waves badly.  Later for the residual of small blocks at
+    // degree 3 (8^2 cells, 1 000 000: 473 against 632 us; 12^2: 876 against 585).
+    if (f->mortar && P >= 1) {
+        if (om == dgk::OUT_RES64 && P == 3 && N <= 8) return 0;
+        return cells <= ((P == 1 && N >= 10) || (P == 2 && N == 12) ? 65536 : 131072) ? 0 : 1;
+    }
+    // otherwise: 28 672 cells, two-level degree 2: 14.4 against 18.0 us; 36 864
+    // cells, degree 1 / 2 / 3: 14.1 / 26.3 / 40.9 against 11.7 / 16.8 / 21.6 us
+    return cells <= 32768 ? 0 : 1;
 }
 
-dgk::StageShape stage_shape(const dgamr_forest *f)
+dgk::StageShape stage_shape(const dgamr_forest *f, int om)
 {
     dgk::StageShape sh;
-    sh.variant = stage_variant(f);
+    sh.variant = stage_variant(f, om);
     sh.rows = f->slab_rows;
     sh.mfma = f->mfma;
     return sh;
@@ -140,7 +160,7 @@ int launch_stage(dgamr_forest *f, dgk::StageArgs a, int gm, int om, hipStream_t 
     if (a.nleaves == 0) return DGAMR_OK;
     const bool fp32 = f->topo.desc().precision == DGAMR_FP32;
     const int eq = f->topo.advection() ? dgk::EQ_ADVECTION : dgk::EQ_EULER;
-    const dgk::StageShape sh = stage_shape(f);
+    const dgk::StageShape sh = stage_shape(f, om);
     return dispatch(f->topo.dim(), f->topo.desc().degree, [&](auto D, auto P) -> int {
         HIP_TRY((dgk::launch_stage<D, P>(a, gm, om, lim, fp32, sh, s, eq)));
         return DGAMR_OK;
