@@ -1179,7 +1179,6 @@ __global__ __launch_bounds__(256) void k_fill(FillArgs g)
         // in the source frame, then the rotation R^n into this leaf's frame
         const RotPlan Rp = g.plans[L.rot - 1 + t];
         double ks[NV][NB];
-#pragma unroll 1
         for (int v = 0; v < NV; ++v) {
             double kv[NB];
             if (Rp.type == dgamr::PLAN_COMBINE) {
@@ -1273,7 +1272,6 @@ __global__ __launch_bounds__(256) void k_fill(FillArgs g)
         }
     } else { // LINK_FINE: 2^d fine cells, 2 along a and 2^(d-1) tangential
         const double *base = g.u + long(link_nbr(L, fine_block(t, N, D))) * NV * sv;
-#pragma unroll 1 // (unrolled, the 3-D unit of degree 3 takes minutes to compile)
         for (int v = 0; v < NV; ++v) {
             double acc[NB];
 #pragma unroll
