@@ -407,7 +407,7 @@ __global__ __launch_bounds__(kThreads3v, waves_3v<P>()) void k_stage3v(StageArgs
             });
             if constexpr (P > 2) load_layer(k + 1, Kn);
             if constexpr (OM == OUT_RK)
-                if (PREFETCH && g.rk_a != 0.0 && real) // uniform: stages 2 and 3 add the RK base state
+                if (PREFETCH && g.rk_a != 0.0) // uniform: stages 2 and 3 add the RK base state
 #pragma unroll
                     for (int m = 0; m < NB; ++m) Un[m] = plane(g.un, m)[uc + unsigned(k * layer)];
         }
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(kThreads3v, waves_3v<P>()) void k_stage3v(StageArgs
                 const double a = g.rk_a, b = g.rk_b;
 #pragma unroll
                 for (int m = 0; m < NB; ++m) K[m] = b * fma(dt * kTab<3, P>.inv_mass[m], R[m], K[m]);
-                if (a != 0.0 && real) { // (uniform) a repeated item stays off un: the last stage writes it in place
+                if (a != 0.0) {
 #pragma unroll
                     for (int m = 0; m < NB; ++m) K[m] = fma(a, PREFETCH ? Un[m] : plane(g.un, m)[idx], K[m]);
                 }
@@ -462,8 +462,9 @@ __global__ __launch_bounds__(kThreads3v, waves_3v<P>()) void k_stage3v(StageArgs
         if (it >= -1) lift_3v<P, 2>(Pt, -1.0, sc[2], R);
     }
     // No rate of a spare slot, whose state took a + face's flux for a - face's,
-    // nor of a repeated item: it is no cell's, and in the last stage (un and
-    // out64 are one array) the item it repeats may have stored its state already
+    // nor of a repeated item, which in the last stage (un and out64 are one
+    // array) may have read what the item it repeats had stored already: what
+    // either computes from there is dropped
     if constexpr (OM == OUT_RK)
         if (g.rate_out) block_max_to(real && is_cell ? rate : 0.0, lds_all, g.rate_out);
 }
