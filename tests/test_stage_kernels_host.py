@@ -16,7 +16,7 @@ CXX = shutil.which("amdclang++") or "/opt/rocm/bin/amdclang++"
 
 
 @pytest.mark.skipif(not os.path.exists(CXX), reason="amdclang++ not found")
-@pytest.mark.parametrize("dim,p,sizes", [(2, 1, "2,6,16"), (2, 3, "6,12"), (3, 1, "2,4"), (3, 2, "2,4"), (3, 3, "2,4")])
+@pytest.mark.parametrize("dim,p,sizes", [(2, 0, "2,6"), (2, 1, "2,6,16"), (2, 3, "6,12"), (3, 0, "2,4"), (3, 1, "2,4"), (3, 2, "2,4"), (3, 3, "2,4")])
 def test_stage_kernels_on_the_host(dim, p, sizes, tmp_path):
     exe = str(tmp_path / "stage_kernels_check")
     cmd = [CXX, "-x", "c++", "-std=c++17", "-O1", "-mfma", "-w", "-fconstexpr-steps=200000000",
