@@ -112,7 +112,7 @@ int stage_rows_options(int N, int *rows, int max_options, bool fp32)
     return n;
 }
 
-template <int D, int P, typename T, int EQ = EQ_EULER, bool MF = false>
+template <int D, int P, typename T, int EQ = EQ_EULER, bool MF = false, bool AXIS = by_axis<D, P, T, EQ>()>
 hipError_t launch_stage_cell(const StageArgs &args, int gm, int om, bool lim, const StageShape &sh, hipStream_t s)
 {
     StageArgs a = args;
@@ -122,7 +122,7 @@ hipError_t launch_stage_cell(const StageArgs &args, int gm, int om, bool lim, co
     int rows = sh.rows;
     if (rows == 0) {
         rows = a.N;
-        if constexpr (by_axis<D, P, T>()) {
+        if constexpr (AXIS) {
             // the slab that fills its waves best; among equals the tallest of
             // at most stage_default_cells cells (12^2-cell blocks, 100^2 roots,
             // degree 2: 4 rows, 48 of 64 lanes, 213 us; 6 rows, 72 of 128, 271;
@@ -149,7 +149,7 @@ hipError_t launch_stage_cell(const StageArgs &args, int gm, int om, bool lim, co
     // the face modes of every slab cell and of the cells outside), and the
     // workgroup maximum of the CFL rate
     size_t lds = sizeof(double) * (D + 2) * face_chunk<D, P>() * nslab;
-    if constexpr (by_axis<D, P, T>()) {
+    if constexpr (AXIS) {
         lds = sizeof(double) * stage_lds_values<D, P, nvar<D, EQ>()>(a.N, rows);
         if (lds < sizeof(double) * size_t(nslab)) lds = sizeof(double) * size_t(nslab);
     }
@@ -172,15 +172,15 @@ hipError_t launch_stage_cell(const StageArgs &args, int gm, int om, bool lim, co
     if constexpr (EQ == EQ_ADVECTION) {
         // one variable: the far side is always taken inline
         if (gm == GUARD_INLINE && om == OUT_RK) {
-            hipLaunchKernelGGL((k_stage<D, P, GUARD_INLINE, OUT_RK, false, T, EQ>), grid_all, block, lds, s, a, rows);
+            hipLaunchKernelGGL((k_stage<D, P, GUARD_INLINE, OUT_RK, false, T, EQ, false, false, AXIS>), grid_all, block, lds, s, a, rows);
             return hipGetLastError();
         }
         if (gm == GUARD_BUFFER && om == OUT_RES64) {
-            hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RES64, false, T, EQ>), grid_all, block, lds, s, a, rows);
+            hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RES64, false, T, EQ, false, false, AXIS>), grid_all, block, lds, s, a, rows);
             return hipGetLastError();
         }
         if (gm == GUARD_BUFFER && om == OUT_RK) { // rotated root frames
-            hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RK, false, T, EQ>), grid_all, block, lds, s, a, rows);
+            hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RK, false, T, EQ, false, false, AXIS>), grid_all, block, lds, s, a, rows);
             return hipGetLastError();
         }
         return hipErrorInvalidValue;
@@ -188,13 +188,13 @@ hipError_t launch_stage_cell(const StageArgs &args, int gm, int om, bool lim, co
     constexpr int GMRK = GUARD_INLINE; // the fused stage takes the far side inline
     if (gm == GMRK && om == OUT_RK) {
         if (persist && lim)
-            hipLaunchKernelGGL((k_stage<D, P, GMRK, OUT_RK, true, T, EQ_EULER, true, MF>), grid, block, lds, s, a, rows);
+            hipLaunchKernelGGL((k_stage<D, P, GMRK, OUT_RK, true, T, EQ_EULER, true, MF, AXIS>), grid, block, lds, s, a, rows);
         else if (persist)
-            hipLaunchKernelGGL((k_stage<D, P, GMRK, OUT_RK, false, T, EQ_EULER, true, MF>), grid, block, lds, s, a, rows);
+            hipLaunchKernelGGL((k_stage<D, P, GMRK, OUT_RK, false, T, EQ_EULER, true, MF, AXIS>), grid, block, lds, s, a, rows);
         else if (lim)
-            hipLaunchKernelGGL((k_stage<D, P, GMRK, OUT_RK, true, T, EQ_EULER, false, MF>), grid, block, lds, s, a, rows);
+            hipLaunchKernelGGL((k_stage<D, P, GMRK, OUT_RK, true, T, EQ_EULER, false, MF, AXIS>), grid, block, lds, s, a, rows);
         else
-            hipLaunchKernelGGL((k_stage<D, P, GMRK, OUT_RK, false, T, EQ_EULER, false, MF>), grid, block, lds, s, a, rows);
+            hipLaunchKernelGGL((k_stage<D, P, GMRK, OUT_RK, false, T, EQ_EULER, false, MF, AXIS>), grid, block, lds, s, a, rows);
         return hipGetLastError();
     }
     if (gm == GUARD_BUFFER && om == OUT_RK) {
@@ -205,21 +205,21 @@ hipError_t launch_stage_cell(const StageArgs &args, int gm, int om, bool lim, co
             return hipErrorNotSupported;
         } else {
             if (lim)
-                hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RK, true, T>), grid_all, block, lds, s, a, rows);
+                hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RK, true, T, EQ_EULER, false, false, AXIS>), grid_all, block, lds, s, a, rows);
             else
-                hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RK, false, T>), grid_all, block, lds, s, a, rows);
+                hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RK, false, T, EQ_EULER, false, false, AXIS>), grid_all, block, lds, s, a, rows);
             return hipGetLastError();
         }
     }
     if constexpr (std::is_same<T, float>::value) {
         if (gm == GUARD_BUFFER && om == OUT_RES32) {
-            hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RES32, false, T, EQ_EULER, false, MF>), grid_all, block,
+            hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RES32, false, T, EQ_EULER, false, MF, AXIS>), grid_all, block,
                                lds, s, a, rows);
             return hipGetLastError();
         }
     } else {
         if (gm == GUARD_BUFFER && om == OUT_RES64) {
-            hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RES64, false, T>), grid_all, block, lds, s, a, rows);
+            hipLaunchKernelGGL((k_stage<D, P, GUARD_BUFFER, OUT_RES64, false, T, EQ_EULER, false, false, AXIS>), grid_all, block, lds, s, a, rows);
             return hipGetLastError();
         }
     }
@@ -230,6 +230,10 @@ hipError_t launch_stage_cell(const StageArgs &args, int gm, int om, bool lim, co
 // defined here, instantiated in parts 1, 2 and 5
 #if DG_D == 3
 extern template hipError_t launch_stage_3v<DG_P>(const StageArgs &, int, int, hipStream_t, int);
+#if DG_P == 0
+extern template hipError_t launch_stage_cell<DG_D, DG_P, double, EQ_EULER, false, false>(const StageArgs &, int, int, bool,
+                                                                                        const StageShape &, hipStream_t);
+#endif
 #endif
 extern template hipError_t launch_stage_cell<DG_D, DG_P, double, EQ_EULER>(const StageArgs &, int, int, bool,
                                                                           const StageShape &, hipStream_t);
@@ -245,7 +249,17 @@ hipError_t launch_stage(const StageArgs &a, int gm, int om, bool lim, bool fp32,
                         int eq)
 {
     if (a.nleaves == 0) return hipSuccess;
-    if (eq == EQ_ADVECTION) return fp32 ? hipErrorInvalidValue : launch_stage_cell<D, P, double, EQ_ADVECTION>(a, gm, om, lim, sh, s);
+    if (eq == EQ_ADVECTION) {
+        if (fp32) return hipErrorInvalidValue;
+        // four-cell blocks of one variable: the dense gather of the far traces
+        // costs more than the contraction saves (degree 1, 8 000 / 500 000 cells:
+        // point by point 23.6 / 350 us a step, axis by axis 27.9 / 381; degree 2:
+        // 33.8 / 633 against 36.3 / 588, 60 000: 88 against 92)
+        if constexpr (D == 2 && (P == 1 || P == 2))
+            if (a.N == 2 && (P == 1 || a.nleaves <= 32768))
+                return launch_stage_cell<D, P, double, EQ_ADVECTION, false, false>(a, gm, om, lim, sh, s);
+        return launch_stage_cell<D, P, double, EQ_ADVECTION>(a, gm, om, lim, sh, s);
+    }
     if (fp32) {
         if constexpr (mfma_volume<D, P>()) {
             // the volume integral on the matrix cores where the slab is whole
@@ -267,6 +281,11 @@ hipError_t launch_stage(const StageArgs &a, int gm, int om, bool lim, bool fp32,
         if (om != OUT_RK && sh.rows > 0 && (a.N % sh.rows != 0 || sh.rows * a.N * 4 > 512)) return hipErrorInvalidValue;
     } else {
         if (lanes_3d(sh, lim, false, a.conservative != 0, false, a.N)) return launch_stage_3v<P>(a, gm, om, s, sh.rows);
+        // degree 0 with mortar faces, whose traces the gather leaves out: point
+        // by point (40 000 cells in 2^3 / 8^3 blocks, one root in ten refined,
+        // 109 / 37 us a step against 115 / 42)
+        if constexpr (P == 0)
+            if (a.conservative) return launch_stage_cell<D, P, double, EQ_EULER, false, false>(a, gm, om, lim, sh, s);
     }
     return launch_stage_cell<D, P, double>(a, gm, om, lim, sh, s);
 }
@@ -404,6 +423,10 @@ template hipError_t launch_stage_3v<DG_P>(const StageArgs &, int, int, hipStream
 #elif DG_PART == 1
 template hipError_t launch_stage_cell<DG_D, DG_P, double, EQ_EULER>(const StageArgs &, int, int, bool,
                                                                    const StageShape &, hipStream_t);
+#if DG_D == 3 && DG_P == 0
+template hipError_t launch_stage_cell<DG_D, DG_P, double, EQ_EULER, false, false>(const StageArgs &, int, int, bool,
+                                                                                 const StageShape &, hipStream_t);
+#endif
 #elif DG_PART == 2
 template hipError_t launch_stage_cell<DG_D, DG_P, float, EQ_EULER>(const StageArgs &, int, int, bool,
                                                                   const StageShape &, hipStream_t);

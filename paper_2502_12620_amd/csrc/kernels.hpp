@@ -1143,9 +1143,11 @@ __device__ __forceinline__ void stage_item(const StageArgs &g, int rows, int ite
 // Whether the stage item contracts axis by axis: FP64, 2-D and 3-D to degree
 // 1.  From degree 2 in 3-D one thread cannot hold the state, the residual
 // and a face's traces and fluxes (16^3 roots, degree 2: 15.2 ms per two steps
-// point by point, 16.2 axis by axis with 440 bytes of spills)
-template <int D, int P, typename T>
-constexpr bool by_axis() { return sizeof(T) == 8 && (D == 2 || P <= 1); }
+// point by point, 16.2 axis by axis with 440 bytes of spills).  Scalar
+// convection at degree 0 has nothing to contract (3-D, 150 000 cells in 2^3 /
+// 8^3 blocks 65 / 22 us a step point by point, 82 / 24 axis by axis).
+template <int D, int P, typename T, int EQ = EQ_EULER>
+constexpr bool by_axis() { return sizeof(T) == 8 && (D == 2 || P <= 1) && (EQ == EQ_EULER || P > 0); }
 
 // the item with the contractions point by point (kernels_points.hpp)
 template <int D, int P, int GM, int OM, bool LIM, typename T, int EQ, bool MF>
@@ -1159,19 +1161,19 @@ __device__ __forceinline__ void stage_item_points(const StageArgs &g, int rows, 
 // multiple of the XCD count every item a workgroup takes maps to the same
 // XCD's leaf range.
 template <int D, int P, int GM, int OM, bool LIM, typename T = double, int EQ = EQ_EULER, bool PERSIST = false,
-          bool MF = false>
+          bool MF = false, bool AXIS = by_axis<D, P, T, EQ>()>
 __global__ __launch_bounds__((stage_threads<D, P, T>()), (stage_min_waves<D, P, T>())) void k_stage(StageArgs g,
                                                                                                      int rows)
 {
     const int total = g.nleaves * (g.N / rows);
     auto run = [&](int item) __attribute__((always_inline)) {
-        if constexpr (by_axis<D, P, T>()) stage_item<D, P, GM, OM, LIM, EQ>(g, rows, item, total);
+        if constexpr (AXIS) stage_item<D, P, GM, OM, LIM, EQ>(g, rows, item, total);
         else stage_item_points<D, P, GM, OM, LIM, T, EQ, MF>(g, rows, item, total);
     };
     if constexpr (PERSIST) {
         for (int item = blockIdx.x; item < total; item += gridDim.x) {
             run(item);
-            if constexpr (by_axis<D, P, T>()) __syncthreads(); // the next item reuses the LDS
+            if constexpr (AXIS) __syncthreads(); // the next item reuses the LDS
         }
     } else { // one item per workgroup: no loop to hold values across items
         run(blockIdx.x);
