@@ -136,6 +136,10 @@ int stage_variant(const dgamr_forest *f, int om)
     }
     // otherwise: 28 672 cells, two-level degree 2: 14.4 against 18.0 us; 36 864
     // cells, degree 1 / 2 / 3: 14.1 / 26.3 / 40.9 against 11.7 / 16.8 / 21.6 us
+    // (at degree 0 in blocks of one wave the workgroups' atomics of the folded
+    // CFL rate count too: three steps of a run on 80 000 cells in 8^2 blocks 84
+    // against 94 us, 125 000: 106 against 96)
+    if (P == 0 && N <= 8 && f->topo.n() <= 1536) return 0;
     return cells <= 32768 ? 0 : 1;
 }
 

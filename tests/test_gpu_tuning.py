@@ -39,7 +39,7 @@ def test_cell_limit_of_the_2d_lane_kernel(N):
 
 # (degree, N, roots, kernel with a hanging face, kernel without)
 MORTAR = [(2, 8, (25, 25), 0, 1), (3, 16, (21, 20), 0, 1), (1, 16, (13, 13), 0, 1), (1, 16, (17, 16), 1, 1),
-          (0, 8, (25, 25), 1, 1)]
+          (0, 16, (13, 13), 1, 1)]
 
 
 @pytest.mark.parametrize("p,N,roots,with_mortar,without", MORTAR)
