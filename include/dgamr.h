@@ -354,9 +354,9 @@ int dgamr_profile_read(dgamr_forest *f, double *stage_ms, int64_t *stage_launche
  * dgamr_pool_bytes for the capacity).  Admit and release enqueue table
  * uploads on the given stream; steps on the same stream see them in order.
  * A released member's slots keep their contents until the next admission.
- * Pools are not thread-safe.  The stage kernel is chosen as for a single
- * forest of the class (3-D degree 3: one lane per (cell, variable); else
- * one thread per cell) until dgamr_pool_set_shape, dgamr_pool_set_lanes or
+ * Pools are not thread-safe.  The stage kernel is one lane per (cell,
+ * variable) in 3-D at degree 3 (FP64 without the limiter or mortar faces) and
+ * one thread per cell otherwise, until dgamr_pool_set_shape, dgamr_pool_set_lanes or
  * dgamr_pool_autotune changes it.
  * --------------------------------------------------------------------- */
 typedef struct dgamr_pool dgamr_pool;
@@ -394,7 +394,8 @@ int dgamr_pool_set_lanes(dgamr_pool *p, int32_t rows);
 /* Autotuner: times the stage kernel on the pool's current members for every
  * allowed (rows, grid) pair of the thread-per-cell kernel and, for the
  * classes dgamr_pool_set_lanes accepts, every slab height of the
- * lane-per-(cell, variable) kernel, and keeps the fastest; writes the choice (variant 1
+ * lane-per-(cell, variable) kernel (in 3-D also rows = 0, its own choice), and
+ * keeps the fastest; writes the choice (variant 1
  * thread per cell, 0 lane per variable; rows; grid) and its average launch
  * time in microseconds (any output pointer may be null).  Synchronous; the state
  * arena is read, the work buffer overwritten. */

@@ -413,7 +413,8 @@ int dgamr_pool_autotune(dgamr_pool *p, double *u_arena, void *work, hipStream_t 
         });
         // FP64 without the limiter (3-D: and without mortar faces) also has
         // the lane-per-(cell, variable) kernel: 2-D slabs of r rows with
-        // 4 r N <= 512 lanes, 3-D slabs of r layers as rows_ok_3v allows
+        // 4 r N <= 512 lanes, 3-D slabs of r layers as rows_ok_3v allows and
+        // the kernel's own choice (0), which may be a taller one
         const bool try_lanes = lanes_class(p);
         PoolWork w = carve(p, work);
         CHECK(pool_dt(p, u_arena, w, stream));
@@ -436,8 +437,8 @@ int dgamr_pool_autotune(dgamr_pool *p, double *u_arena, void *work, hipStream_t 
                 if (gsz == 0 || gsz < items) cands.push_back({1, opts[oi], gsz});
         }
         if (try_lanes)
-            for (int r = p->N; r >= 1; --r)
-                if (lanes_rows_ok(p, r)) cands.push_back({0, r, 0});
+            for (int r = p->N; r >= 0; --r)
+                if (r == 0 ? p->dim == 3 : lanes_rows_ok(p, r)) cands.push_back({0, r, 0});
         for (size_t ci = 0; ci < cands.size() && rc == DGAMR_OK; ++ci) {
             {
                 dgk::StageShape sh;
