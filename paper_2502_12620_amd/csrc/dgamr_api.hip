@@ -127,12 +127,21 @@ int stage_variant(const dgamr_forest *f, int om)
     // degree 3 114 / 151 against 322 / 205; at 125 000: 125 / 168 against 129 / 180
     // and 228 / 277 against 313 / 418; at 300 000: 237 / 339 against 213 / 220 and
     // 454 / 573 against 563 / 533.  Earlier at degree 1 (10^2 cells, 80 000: 74
-    // against 67) and on 12^2 cells (degree 2, 80 000: 158 against 126), whose rows
-    // fill the lanes' waves badly.  Later for the residual of small blocks at
-    // degree 3 (8^2 cells, 1 000 000: 473 against 632 us; 12^2: 876 against 585).
+    // against 67; 8^2, 100 000: 68 against 63) and on 12^2 cells (degree 1 / 2 at
+    // 60 000: 76 / 132 against 65 / 129), whose rows fill the lanes' waves badly.  Later for the
+    // residual, which has no base state to read, from degree 2 (6^2 / 8^2 / 16^2
+    // cells: degree 2 at 200 000 70 / 55 / 73 against 82 / 72 / 62; degree 3 at 150 000
+    // on 8^2 / 16^2 80 / 91 against 148 / 144, at 300 000 on 16^2 174 against 160, on
+    // 8^2 at any count, 1 000 000: 473 against 632).
     if (f->mortar && P >= 1) {
-        if (om == dgk::OUT_RES64 && P == 3 && N <= 8) return 0;
-        return cells <= ((P == 1 && N >= 10) || (P == 2 && N == 12) ? 65536 : 131072) ? 0 : 1;
+        const bool res = om == dgk::OUT_RES64;
+        if (res && P == 3 && N <= 8) return 0;
+        long line = 131072;
+        if (P <= 2 && N == 12) line = P == 1 ? 32768 : 49152;
+        else if (P == 1 && N >= 8) line = N >= 10 ? 65536 : 98304;
+        else if (res && P == 2) line = N <= 8 ? 262144 : (N == 16 ? 196608 : line);
+        else if (res && P == 3 && N != 12) line = 262144;
+        return cells <= line ? 0 : 1;
     }
     // otherwise: 28 672 cells, two-level degree 2: 14.4 against 18.0 us; 36 864
     // cells, degree 1 / 2 / 3: 14.1 / 26.3 / 40.9 against 11.7 / 16.8 / 21.6 us
