@@ -820,7 +820,9 @@ constexpr int stage_threads() { return (D == 3 && P <= 1) ? 512 : 256; }
 // at 2-D degree 3, which runs one wave per SIMD (40^2 roots of 16^2 cells:
 // degree 1 64 / 128 / 256 cells 32.7 / 30.7 / 32.3 us; degree 2 57.7 / 54.7 /
 // 60.8; degree 3 124.6 / 136.8 / 152.6; 3-D degree 1, 12^3 roots of 8^3 cells
-// 128 / 256 / 512 cells 153 / 150 / 183 us).  Point by point: 3-D degree 2 in
+// 128 / 256 / 512 cells 153 / 150 / 183 us); 2-D degree 0, whose work is the
+// smallest against a workgroup's own (the folded rate's atomic), 192 (12^2-cell
+// blocks, 150 000 cells, a run of three steps: 144 cells 90 us, 48 118).  Point by point: 3-D degree 2 in
 // FP64 128 cells (256: 2.68 -> 2.53 ms on 16^3 roots), in FP32 the whole budget
 // (2.18 against 2.21 ms), as at degree 3, and 128 cells for the other FP32
 // kernels below.
@@ -828,8 +830,8 @@ template <int D, int P, typename T = double>
 constexpr int stage_default_cells()
 {
     if (D == 2 && P == 3 && sizeof(T) == 8) return 64;
-    return ((D == 3 && P <= 1) || (D == 3 && P == 2 && sizeof(T) == 8) || (D == 2 && (P == 1 || P == 2)) ||
-            (D == 2 && P == 0 && sizeof(T) == 8))
+    if (D == 2 && P == 0 && sizeof(T) == 8) return 192;
+    return ((D == 3 && P <= 1) || (D == 3 && P == 2 && sizeof(T) == 8) || (D == 2 && (P == 1 || P == 2)))
                ? 128
                : stage_threads<D, P, T>();
 }
