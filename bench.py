@@ -3,7 +3,7 @@
 One step = one full SSP-RK3 time step of the 2-D Euler two-level AMR vortex
 workload (8x8 roots of 16x16 cells, the 12 roots near the vortex refined
 once -> 100 leaves, degree 2, FP64): the CFL time step and, per stage, the
-guard traces, the residual and the stage update.  The timed steps are one
+far side of every block face, the residual and the stage update.  The timed steps are one
 launch of a HIP graph holding them: three fused stage kernels per step, the
 CFL reduction folded into the previous step's last stage.
 

@@ -72,7 +72,11 @@ hipError_t launch_stage_3v(const StageArgs &args, int gm, int om, hipStream_t s,
     if (rows > 0) {
         if (!rows_ok_3v(N, rows)) return hipErrorInvalidValue;
     } else {
-        // whole leaves, in thinner slabs until every compute unit has work
+        // whole leaves, in thinner slabs (which take a z face more each) until
+        // there are 1024 items, four a compute unit: 8^3 cells, degree 3, a step on
+        // 720 leaves in half blocks 4.46 ms, whole 5.21; 512 leaves in half blocks
+        // 3.07, whole 2.86, in quarters 3.39; 4^3 cells, 512 leaves 0.51 in half
+        // blocks, 0.66 whole; 1024 or more leaves whole (1452: 1.29, half blocks 1.47)
         rows = N;
         while (rows % 2 == 0 && long(a.nleaves) * (N / rows) < 1024) rows /= 2;
     }

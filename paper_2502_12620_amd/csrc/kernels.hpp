@@ -896,7 +896,7 @@ __device__ __forceinline__ void stage_item(const StageArgs &g, int rows, int ite
     // contracted at a time: planes (3-D), rows along x, points.  R is the
     // right-hand side of the weak form; M^-1 (diagonal) follows at the end.
     const double gamma = g.gamma, gm1 = g.gamma - 1.0;
-    // scalar convection: the velocity along the leaf's local axes, Q^double vel
+    // scalar convection: the velocity along the leaf's local axes, Q^T vel
     // (Sec. 3.1 frames; the identity on aligned roots)
     struct {
         double vel[3];

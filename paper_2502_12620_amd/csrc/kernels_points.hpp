@@ -7,9 +7,13 @@
 //    take 100 (degree 2) or 200 of its 256 doubles.  At degree 3 the
 //    axis-by-axis form spills 2.7 KB per lane and 13 000 scalars, and one of
 //    its builds returned wrong momenta in the residual of a conservative
-//    hanging forest (the same source, compiled otherwise, passed).  Steps
-//    run one lane per (cell, variable) there (kernels_3d.hpp) unless they have
-//    the limiter or mortar faces.
+//    hanging forest.  Its source is right: compiled for the host it agrees with
+//    this item to 2e-15 there, whatever the order of the threads between
+//    barriers and the contents of LDS (tests/native/stage_kernels_check.cpp),
+//    as do the instances in use, none of whose residuals spills to memory.
+//    What that build did wrong on the GPU is not known.  Steps run one lane per
+//    (cell, variable) there (kernels_3d.hpp) unless they have the limiter or
+//    mortar faces.
 #pragma once
 
 #include "kernels.hpp"

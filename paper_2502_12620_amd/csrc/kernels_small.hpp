@@ -75,8 +75,8 @@ static __global__ __launch_bounds__(1024) void k_dt_final(const double *leaf_max
 
 // dt of a small forest in one launch (a launch's own latency bounds it, about
 // 3 us): one workgroup takes the CFL rate of every cell (k_rate's arithmetic; the maximum does not depend on the order)
-// and writes dt = cfl / max, with the maximum in leaf_max[0] for leaf_max ==
-// 0 .. n - 1 (k_rate_slot reads them all).
+// and writes dt = cfl / max, and the forest's maximum to every entry
+// leaf_max[0 .. n - 1] (k_rate_slot reads them all).
 template <int D>
 __global__ __launch_bounds__(1024) void k_rate_small(const double *u, const LeafGeo *geo, int N, int nb, int n,
                                                      double gamma, double cfl, double *leaf_max, double *dt)

@@ -9,8 +9,8 @@
 
 namespace dgk {
 
-// Launch shape of the stage kernel.  variant (FP64 without the limiter;
-// 2-D any output, 3-D the fused stage without mortar faces): 0 = one lane
+// Launch shape of the stage kernel.  variant (FP64 without the limiter, in
+// 3-D without mortar faces; residual or fused stage): 0 = one lane
 // per (cell, variable) in slabs of rows (2-D) or layers (3-D), 1 = one
 // thread per cell.  rows: layers of the last axis per workgroup (0 = the
 // kernel's own choice); grid: workgroups of a persistent launch of the
@@ -26,7 +26,7 @@ struct StageShape {
 // a block and its N + faces at a time, 6 waves at N = 8; a workgroup holds
 // as many blocks as make a multiple of four waves (two at N = 8).  A slab
 // height asked for: whole layers, at least two unless it is the whole leaf,
-// at most 144 cells.
+// at most 144 cells (the kernel's own choice, 0, may be any divisor of N).
 constexpr int kCells3v = 12;
 constexpr int kThreads3v = 768;
 inline bool rows_ok_3v(int N, int rows)
