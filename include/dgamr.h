@@ -304,8 +304,9 @@ int dgamr_check_state(dgamr_forest *f, const double *u, int64_t *bad, void *work
  *     forests always run variant 1): variant 0 in slabs of layers, automatic
  *     from degree 2;
  *   DGAMR_TUNE_VAR_SPLIT_MAX_CELLS: the automatic 2-D choice uses variant 0
- *     up to this many cells (until it is set: up to 32768, and at every count
- *     on blocks of at most 4^2 cells);
+ *     up to this many cells (until it is set: up to 32768, at every count on
+ *     blocks of at most 4^2 cells, and further on conservative forests with
+ *     hanging faces and at degree 0);
  *   DGAMR_TUNE_SLAB_ROWS: layers of the block's last axis per stage
  *     workgroup (0 automatic, else a divisor of n_cell within the kernel's
  *     thread budget; a launch that does not fit fails with DGAMR_EHIP);
